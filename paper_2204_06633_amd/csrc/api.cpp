@@ -45,6 +45,30 @@ int carry_row_capacity(int order, double spread, double dt, int rows, int ncarry
   return bytes <= (size_t)150 * 1024 ? cap : 0;
 }
 
+// The filters need positive light times (every delayed stencil then ends
+// before tap o + N / 2) and rows that fit LDS.  Elsewhere the faster kernel is
+// taken, from the times (us) of both on one MI355X: 3,155,760 samples where
+// the device is full, 32,768 (latency) below 2^19; filters linear in the taps,
+// one-by-one kernels in N.  At order 25 and dt = 10 s (32 taps): generation 2
+// forward 232 against 535, adjoint 260 against 842; generation 1 forward 202
+// against 254; 32,768 samples of generation 2 20.8 against 40.8.  At dt = 2 s
+// the taps outgrow N and low orders and generation 1 stay with the streams.
+FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt, int64_t n,
+                       bool adjoint) {
+  const int N = order + 1;
+  const double s = std::ceil((gen == 1 ? 3 : 7) * L_max / dt);
+  if (!(L_min > 0.0) || !(s < 40.0)) return {0, 0};
+  const int taps = (N - 1 + (int)s + 1) & ~1;
+  // {intercept, slope}: filters, one by one in generation 1 and 2
+  constexpr double fwd[2][6] = {{8.5, 0.38, 12.0, 0.31, 20.0, 0.68},
+                                {33.0, 6.2, 66.0, 7.4, 85.0, 17.6}};
+  constexpr double adj[2][6] = {{9.0, 0.45, 22.0, 0.5, 30.0, 1.1},
+                                {47.0, 6.65, 170.0, 11.9, 165.0, 26.0}};
+  const double* t = (adjoint ? adj : fwd)[n > ((int64_t)1 << 19)];
+  if (t[0] + t[1] * taps > t[2 * gen] + t[2 * gen + 1] * N) return {0, 0};
+  return {-(int)s - (N / 2 - 1), taps};
+}
+
 }  // namespace lr
 
 namespace {
@@ -392,6 +416,10 @@ int lr_tdi_combine(const lr_orbits* orb, double t0_y, double dt, int64_t n_y, co
   a.n_out = n_out;
   a.channels = channels;
   a.out = out;
+  const lr::FirShape fs = lr::tdi_fir_shape(order, generation, orb->L_min, orb->L_max, dt,
+                                            n_out, false);
+  a.fir_lo = fs.lo;
+  a.fir_k = fs.taps;
   hipError_t e = lr::run_tdi(order, generation, a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "lr_tdi_combine launch");
   return LR_OK;
@@ -409,8 +437,13 @@ int lr_tdi_adjoint(const lr_orbits* orb, double t0_y, double dt, int64_t n_y, in
   if (overlap(g_y, 6 * n_y * sizeof(double), g_out, rows * n_out * sizeof(double)))
     return fail(LR_E_ARG, "g_y overlaps g_out");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = lr::run_fill_zero(g_y, 6 * n_y, s);
-  if (e != hipSuccess) return hip_fail(e, "lr_tdi_adjoint fill");
+  const lr::FirShape fs = lr::tdi_fir_shape(order, generation, orb->L_min, orb->L_max, dt,
+                                            n_y, true);
+  hipError_t e;
+  if (fs.taps == 0 || n_out == 0) {
+    e = lr::run_fill_zero(g_y, 6 * n_y, s);
+    if (e != hipSuccess) return hip_fail(e, "lr_tdi_adjoint fill");
+  }
   if (n_out == 0) return LR_OK;
   lr::TdiAdjArgs a;
   a.orb = view_of(orb);
@@ -424,6 +457,8 @@ int lr_tdi_adjoint(const lr_orbits* orb, double t0_y, double dt, int64_t n_y, in
   a.n_out = n_out;
   a.g_y = g_y;
   a.rl_cap = lr::carry_row_capacity(order, (generation == 1 ? 3 : 7) * orb->L_max, dt, 6, 2, 0);
+  a.fir_lo = fs.lo;
+  a.fir_k = fs.taps;
   e = lr::run_tdi_adjoint(order, generation, a, s);
   if (e != hipSuccess) return hip_fail(e, "lr_tdi_adjoint launch");
   return LR_OK;

@@ -25,6 +25,7 @@ __device__ __forceinline__ TdiAdjArgs batch_tdi_args(const BatchAdjArgs& a,
   x.n_out = T.n_out;
   x.g_y = a.g_y + T.gy_off;
   x.rl_cap = 0;
+  x.fir_lo = x.fir_k = 0;
   return x;
 }
 

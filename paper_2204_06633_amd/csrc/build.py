@@ -22,6 +22,7 @@ TARGET = os.path.join(PKG, "_lisaresp.so")
 # spread evenly over the compile jobs.
 FUSED_UNITS = [(g, nt) for nt in range(2, 33, 2) for g in (1, 2)]
 SOURCES = (["forward_%s.hip" % k for k in "abcd"] + ["adjoint_%s.hip" % k for k in "abcd"] +
+           ["tdifir_%s.hip" % k for k in "abcd"] +
            ["batchfwd%d_n%d.hip" % u for u in FUSED_UNITS] +
            ["batchadj_%s.hip" % k for k in "abcd"] +
            ["util.hip", "fd_kernels.hip", "gb_kernels.hip", "dispatch.cpp", "api.cpp", "api_batch.cpp",
@@ -33,7 +34,7 @@ def _weight(src):
     """Rough compile cost of a unit (for the job order)."""
     if src.startswith("batchfwd"):
         return 10 + int(src.split("_n")[1][:-4])
-    return 30 if src.startswith(("adjoint", "batchadj", "forward")) else 1
+    return 30 if src.startswith(("adjoint", "batchadj", "forward", "tdifir")) else 1
 
 
 def hipcc():

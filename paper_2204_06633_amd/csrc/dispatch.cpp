@@ -19,7 +19,11 @@ hipError_t run_project_links(int order, const ProjArgs& a, hipStream_t s) {
 
 hipError_t run_tdi(int order, int gen, const TdiArgs& a, hipStream_t s) {
   switch (order) {
-#define X(ORD, NT) case ORD: return launch_tdi<NT>(a, gen, s);
+#define X(ORD, NT)                                                             \
+  case ORD:                                                                    \
+    if (a.fir_k > 0)                                                           \
+      return gen == 1 ? launch_tdi_fir<NT, 1>(a, s) : launch_tdi_fir<NT, 2>(a, s); \
+    return launch_tdi<NT>(a, gen, s);
     LR_ORDER_CASES(X)
 #undef X
     default: return hipErrorInvalidValue;
@@ -28,7 +32,12 @@ hipError_t run_tdi(int order, int gen, const TdiArgs& a, hipStream_t s) {
 
 hipError_t run_tdi_adjoint(int order, int gen, const TdiAdjArgs& a, hipStream_t s) {
   switch (order) {
-#define X(ORD, NT) case ORD: return launch_tdi_adjoint<NT>(a, gen, s);
+#define X(ORD, NT)                                                             \
+  case ORD:                                                                    \
+    if (a.fir_k > 0)                                                           \
+      return gen == 1 ? launch_tdi_fir_adjoint<NT, 1>(a, s)                    \
+                      : launch_tdi_fir_adjoint<NT, 2>(a, s);                   \
+    return launch_tdi_adjoint<NT>(a, gen, s);
     LR_ORDER_CASES(X)
 #undef X
     default: return hipErrorInvalidValue;

@@ -29,6 +29,9 @@ struct TdiArgs {
   int64_t out_start, n_out;
   int channels;      // LR_XYZ, LR_AET or LR_XYZ_AET
   double* out;       // [3 or 6][n_out]
+  // TDI filters: taps o + fir_lo .. + fir_k - 1 of output o; fir_k 0: one
+  // stream per delay instead
+  int fir_lo, fir_k;
 };
 
 struct TdiAdjArgs {
@@ -39,8 +42,9 @@ struct TdiAdjArgs {
   double t_off;         // t0_y - (time of coarse orbit sample 0)
   double dt, inv_dt;
   int64_t out_start, n_out;
-  double* g_y;          // [6][n_y], zero-filled before the launch
+  double* g_y;          // [6][n_y], zero-filled before the launch (filters: written whole)
   int rl_cap;           // wave row capacity of the carry kernel (even); 0: atomic kernel
+  int fir_lo, fir_k;    // as in TdiArgs; fir_k 0: scatter kernels
 };
 
 struct ProjAdjArgs {
@@ -71,6 +75,10 @@ hipError_t launch_project(const ProjArgs& a, hipStream_t s);
 template <int N>
 hipError_t launch_tdi(const TdiArgs& a, int gen, hipStream_t s);
 
+template <int N, int GEN>
+hipError_t launch_tdi_fir(const TdiArgs& a, hipStream_t s);
+template <int N, int GEN>
+hipError_t launch_tdi_fir_adjoint(const TdiAdjArgs& a, hipStream_t s);
 template <int N>
 hipError_t launch_tdi_adjoint(const TdiAdjArgs& a, int gen, hipStream_t s);
 template <int N>
@@ -83,6 +91,15 @@ int set_error(int status, const char* fmt, ...);
 // `spread` seconds (rows per wave, concurrent carries, further doubles of LDS
 // per wave), or 0 if the rows do not fit LDS.
 int carry_row_capacity(int order, double spread, double dt, int rows, int ncarry, int extra);
+
+// Shape of the TDI filters (tdi_fir.hpp) for n samples: first tap relative to
+// the output and taps (even); taps = 0 where the delays are better interpolated
+// one by one.
+struct FirShape {
+  int lo, taps;
+};
+FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt, int64_t n,
+                       bool adjoint);
 
 // Workgroup size of the tiled kernels (output samples per workgroup).
 constexpr int kTile = 256;
