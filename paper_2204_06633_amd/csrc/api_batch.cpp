@@ -173,7 +173,10 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
   }
 
   // TDI adjoint: templates paired by duration (longer first), one work item
-  // per (pair, tile) of the longer one
+  // per (pair, tile) of the longer one: tiles of outputs that scatter, or of
+  // link samples that gather where the filters serve
+  const bool gather = adjoint && lr::tdi_fir_shape(order, generation, tdi->L_min, tdi->L_max, dt,
+                                                   P.gy_doubles / 6, true).taps > 0;
   for (int64_t q = 0; q < n; q += 2) {
     const int64_t b0 = order_idx[q], b1 = q + 1 < n ? order_idx[q + 1] : -1;
     const int64_t pr = (int64_t)P.pairs.size() / 2;
@@ -183,7 +186,8 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
       P.tdi_items.push_back(pr);
       P.tdi_items.push_back(tl);
     }
-    for (int64_t tl = 0; tl < (t[b0].n_out + kCarryTile - 1) / kCarryTile; ++tl) {
+    const int64_t len = gather ? P.adj[b0].n_y : t[b0].n_out;
+    for (int64_t tl = 0; tl < (len + kCarryTile - 1) / kCarryTile; ++tl) {
       P.tdi_citems.push_back(pr);
       P.tdi_citems.push_back(tl);
     }
@@ -275,6 +279,27 @@ int launch_forward(const lr_batch* b, const double* hp, const double* hc, const 
                               b->blocks, s);
   if (e != hipSuccess) return set_error(LR_E_HIP, "lr_response launch: %s", hipGetErrorString(e));
   return LR_OK;
+}
+
+// Channel gradients -> the link-gradient workspace of every template: filters
+// (which write it whole), else carry kernels (deterministic) where their rows
+// fit LDS, else atomic ones.
+hipError_t batch_tdi_adjoint(const lr_batch* b, lr::BatchAdjArgs a, hipStream_t s) {
+  const lr::FirShape fs = lr::tdi_fir_shape(b->order, b->generation, b->tdi.L_min, b->tdi.L_max,
+                                            b->dt, b->gy_doubles / 6, true);
+  a.fir_lo = fs.lo;
+  a.fir_k = fs.taps;
+  if (fs.taps == 0) {
+    const hipError_t e = lr::run_fill_zero(at<double>(b, R_GY), b->gy_doubles, s);
+    if (e != hipSuccess) return e;
+  }
+  if (b->n_tdi_items == 0) return hipSuccess;
+  a.rl_cap = lr::carry_row_capacity(b->order, (b->generation == 1 ? 3 : 7) * b->tdi.L_max, b->dt,
+                                    12, 4, 0);
+  const bool wide = fs.taps > 0 || a.rl_cap > 0;
+  a.items = at<const int64_t>(b, wide ? R_TDI_CITEMS : R_TDI_ITEMS);
+  return lr::run_batch_tdi_adjoint(b->order, b->generation, a,
+                                   wide ? b->n_tdi_citems : b->n_tdi_items, s);
 }
 
 }  // namespace
@@ -423,7 +448,6 @@ int lr_response_adjoint(const lr_batch* b, const double* hp, const double* hc,
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = lr::run_fill_zero(g_hp, b->h_extent, s);
   if (e == hipSuccess) e = lr::run_fill_zero(g_hc, b->h_extent, s);
-  if (e == hipSuccess) e = lr::run_fill_zero(at<double>(b, R_GY), b->gy_doubles, s);
   if (e == hipSuccess && g_sky) e = lr::run_fill_zero(g_sky, 2 * b->n_templates, s);
   lr::BatchAdjArgs a;
   a.orb_p = view(b->proj);
@@ -447,16 +471,8 @@ int lr_response_adjoint(const lr_batch* b, const double* hp, const double* hc,
   a.sky_stride = 2;
   a.params = nullptr;
   a.gb_part = nullptr;
-  // carry kernels (deterministic) where their rows fit LDS, else atomic ones
-  const int cap_t = lr::carry_row_capacity(b->order, (b->generation == 1 ? 3 : 7) * b->tdi.L_max,
-                                           b->dt, 12, 4, 0);
   const int cap_p = lr::carry_row_capacity(b->order, 2.01 * b->proj.L_max, b->dt, 2, 2, 21 * 64);
-  if (e == hipSuccess && b->n_tdi_items > 0) {
-    a.rl_cap = cap_t;
-    a.items = at<const int64_t>(b, cap_t > 0 ? R_TDI_CITEMS : R_TDI_ITEMS);
-    e = lr::run_batch_tdi_adjoint(b->order, b->generation, a,
-                                  cap_t > 0 ? b->n_tdi_citems : b->n_tdi_items, s);
-  }
+  if (e == hipSuccess) e = batch_tdi_adjoint(b, a, s);
   if (e == hipSuccess && b->n_proj_items > 0) {
     a.rl_cap = cap_p;
     a.items = at<const int64_t>(b, cap_p > 0 ? R_PADJ_CITEMS : R_PROJ_ITEMS);
@@ -482,14 +498,11 @@ int lr_response_adjoint_gb(const lr_batch* b, const double* params, const double
   if (pb && (reinterpret_cast<uintptr_t>(g_params) < reinterpret_cast<uintptr_t>(params) + pb &&
              reinterpret_cast<uintptr_t>(params) < reinterpret_cast<uintptr_t>(g_params) + pb))
     return set_error(LR_E_ARG, "g_params overlaps params");
-  const int cap_t = lr::carry_row_capacity(b->order, (b->generation == 1 ? 3 : 7) * b->tdi.L_max,
-                                           b->dt, 12, 4, 0);
   const int cap_p = lr::carry_row_capacity(b->order, 2.01 * b->proj.L_max, b->dt, 2, 2, 21 * 64);
   if (cap_p == 0)
     return set_error(LR_E_UNSUPPORTED, "dt = %g s is too small for the parameter adjoint (the "
                                        "projection footprints do not fit LDS)", b->dt);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = lr::run_fill_zero(at<double>(b, R_GY), b->gy_doubles, s);
   lr::BatchAdjArgs a;
   a.orb_p = view(b->proj);
   a.orb_t = view(b->tdi);
@@ -512,12 +525,7 @@ int lr_response_adjoint_gb(const lr_batch* b, const double* params, const double
   a.gb_part = at<double>(b, R_GB_PART);
   a.pairs = at<const int64_t>(b, R_PAIRS);
   a.sky_items = at<const int64_t>(b, R_PROJ_ITEMS);
-  if (e == hipSuccess && b->n_tdi_items > 0) {
-    a.rl_cap = cap_t;
-    a.items = at<const int64_t>(b, cap_t > 0 ? R_TDI_CITEMS : R_TDI_ITEMS);
-    e = lr::run_batch_tdi_adjoint(b->order, b->generation, a,
-                                  cap_t > 0 ? b->n_tdi_citems : b->n_tdi_items, s);
-  }
+  hipError_t e = batch_tdi_adjoint(b, a, s);
   if (e == hipSuccess && b->n_proj_items > 0) {
     a.rl_cap = cap_p;
     a.items = at<const int64_t>(b, R_PADJ_CITEMS);

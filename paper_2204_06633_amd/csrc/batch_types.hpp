@@ -83,6 +83,7 @@ struct BatchAdjArgs {
   int sky_stride;               // lam, beta of template k at sky[sky_stride * k + 0, 1]
   const double* params;         // [n][8] or null: waveform mode (see ProjAdjArgs)
   double* gb_part;              // waveform mode: [n_items][7] parameter-gradient sums
+  int fir_lo, fir_k;            // TDI filters (see TdiArgs); fir_k 0: scatter kernels
 };
 
 // Launchers (instantiated per tap count in batch_*.hip).
@@ -92,6 +93,8 @@ template <int N, int GEN, int M, int BLOCK, bool WAVE>
 int fused_occupancy();
 template <int N, int GEN>
 hipError_t launch_batch_tdi_adjoint(const BatchAdjArgs& a, int64_t n_items, hipStream_t s);
+template <int N, int GEN>
+hipError_t launch_batch_tdi_fir_adjoint(const BatchAdjArgs& a, int64_t n_items, hipStream_t s);
 template <int N>
 hipError_t launch_batch_project_adjoint(const BatchAdjArgs& a, int64_t n_items,
                                         int64_t n_sky_items, hipStream_t s);

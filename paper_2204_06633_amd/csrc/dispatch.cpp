@@ -115,6 +115,9 @@ hipError_t run_batch_tdi_adjoint(int order, int gen, const BatchAdjArgs& a, int6
   switch (order) {
 #define X(ORD, NT) \
   case ORD:        \
+    if (a.fir_k > 0)                                                           \
+      return gen == 1 ? launch_batch_tdi_fir_adjoint<NT, 1>(a, n_items, s)     \
+                      : launch_batch_tdi_fir_adjoint<NT, 2>(a, n_items, s);    \
     return gen == 1 ? launch_batch_tdi_adjoint<NT, 1>(a, n_items, s) \
                     : launch_batch_tdi_adjoint<NT, 2>(a, n_items, s);
     LR_ORDER_CASES(X)

@@ -29,7 +29,7 @@
 
 #include <float.h>
 
-#include "adjoint_kernels.hpp"
+#include "batch_adjoint_kernels.hpp"
 
 namespace lr {
 
@@ -632,10 +632,39 @@ hipError_t launch_tdi_fir_adjoint(const TdiAdjArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Batches: a pair of templates (sorted by duration) per work item shares the
+// tables; every tile of the longer one's link samples is an item.  Measured on
+// 12 templates of up to 788,941 outputs with the projection adjoint after it:
+// 2.54 -> 1.81 ms, against the pairs of scatters that shared weight sequences.
+template <int N, int GEN>
+__global__ __launch_bounds__(kBlock, 4) void batch_tdi_fir_adjoint_kernel(BatchAdjArgs a) {
+  extern __shared__ double lds_dyn[];
+  __shared__ FirShared sh;
+  const int64_t pr = a.items[2 * blockIdx.x], tile = a.items[2 * blockIdx.x + 1];
+  const int64_t b0 = a.pairs[2 * pr], b1 = a.pairs[2 * pr + 1];
+  TdiAdjArgs x[2] = {batch_tdi_args(a, a.tpl[b0]), batch_tdi_args(a, a.tpl[b1 >= 0 ? b1 : b0])};
+  x[0].fir_lo = x[1].fir_lo = a.fir_lo;
+  x[0].fir_k = x[1].fir_k = a.fir_k;
+  const bool live[2] = {true, b1 >= 0 && tile * kFwdTile < x[1].n_y};
+  tdi_fir_adjoint_tile<N, GEN, 2>(x, live, tile, lds_dyn, sh);
+}
+
+template <int N, int GEN>
+hipError_t launch_batch_tdi_fir_adjoint(const BatchAdjArgs& a, int64_t n_items, hipStream_t s) {
+  const size_t bytes = fir_lds_doubles(6, a.fir_k) * sizeof(double);
+  hipLaunchKernelGGL((batch_tdi_fir_adjoint_kernel<N, GEN>), dim3((unsigned)n_items), dim3(kBlock),
+                     bytes, s, a);
+  return hipGetLastError();
+}
+
 #define LR_INSTANTIATE_FIR(NT)                                                       \
   template hipError_t launch_tdi_fir<NT, 1>(const TdiArgs&, hipStream_t);            \
   template hipError_t launch_tdi_fir<NT, 2>(const TdiArgs&, hipStream_t);            \
   template hipError_t launch_tdi_fir_adjoint<NT, 1>(const TdiAdjArgs&, hipStream_t); \
-  template hipError_t launch_tdi_fir_adjoint<NT, 2>(const TdiAdjArgs&, hipStream_t);
+  template hipError_t launch_tdi_fir_adjoint<NT, 2>(const TdiAdjArgs&, hipStream_t); \
+  template hipError_t launch_batch_tdi_fir_adjoint<NT, 1>(const BatchAdjArgs&, int64_t, \
+                                                          hipStream_t);              \
+  template hipError_t launch_batch_tdi_fir_adjoint<NT, 2>(const BatchAdjArgs&, int64_t, \
+                                                          hipStream_t);
 
 }  // namespace lr
