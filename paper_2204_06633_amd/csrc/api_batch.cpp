@@ -22,19 +22,21 @@ constexpr int kYTileDefault = 512;    // link samples per fused tile (2 per lane
 constexpr int kMaxSegment = 64;       // tiles per fused work item (segment)
 constexpr int64_t kAdjTile = 256;     // samples per adjoint work item (atomic kernels, sky)
 constexpr int64_t kCarryTile = 512;   // samples per work item of the carry adjoint kernels
+constexpr int64_t kFirOutputs = 512;  // outputs per TDI filter table
 constexpr int64_t kLikeChunk = 8192;  // elements per likelihood work item
 
 enum Region {
   R_TPL, R_ITEMS, R_COUNTER, R_ADJ_TPL, R_TDI_ITEMS, R_PROJ_ITEMS, R_SKY_PART, R_SKY_SPAN,
   R_LIKE_ITEMS, R_LIKE_PART, R_LIKE_SPAN, R_PAIRS, R_TDI_CITEMS, R_PADJ_CITEMS, R_GB_PART,
-  R_PADJ_SPAN, R_GY, R_TRIG, R_COUNT
+  R_PADJ_SPAN, R_GY, R_TRIG, R_FIR, R_FIR_SPLIT, R_COUNT
 };
 
 static_assert(R_COUNT <= (int)(sizeof(((lr_batch*)nullptr)->off) / sizeof(size_t)),
               "lr_batch.off has a slot per workspace region");
 
 struct Plan {
-  int F = 0, B = 0, T_out = 0, Y = 0, K = 1;
+  int F = 0, B = 0, T_out = 0, T_first = 0, Y = 0, K = 1;
+  lr::FirShape fir = {0, 0};
   std::vector<lr::BatchTemplate> tpl;
   std::vector<int> items;
   std::vector<lr::BatchAdjTemplate> adj;
@@ -59,9 +61,25 @@ bool fused_variant_exists(int group, int tile, bool wave) {
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
+// Outputs of a segment's first tile, of at most T_out: whole rows of 16 lanes
+// where the TDI filters serve, since the lanes of a row share a table.
+int first_tile(int T_out, int order, int generation, const lr_orbits& tdi, double dt,
+               lr::FirShape& fir) {
+  fir = lr::fused_fir_shape(order, generation, tdi.L_min, tdi.L_max, dt);
+  if (T_out < 32) fir = {0, 0};
+  return fir.taps > 0 ? T_out & ~31 : T_out;
+}
+
+size_t fir_table_bytes(const lr::FirShape& fir) {
+  return (size_t)192 * lr::fir_quads(fir.taps) * sizeof(double);
+}
+
+int64_t fir_intervals(const lr::FirShape& fir, int64_t max_n_out) {
+  return fir.taps > 0 ? (max_n_out + kFirOutputs - 1) / kFirOutputs : 0;
+}
+
 int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, int order,
-              int generation, int channels, int group, int tile, int segment, int adjoint,
-              Plan& P) {
+              int generation, int channels, int group, int tile, int segment, int adjoint, Plan& P) {
   if (n < 0 || (n > 0 && !t)) return set_error(LR_E_ARG, "bad template list");
   if (group != 1 && group != 2 && group != 4)
     return set_error(LR_E_UNSUPPORTED, "group %d (1, 2 or 4 templates per work item)", group);
@@ -84,6 +102,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
     return set_error(LR_E_UNSUPPORTED, "dt = %g s is too small for the fused kernel (the TDI "
                                        "stencil needs %lld + %lld of %d link samples)",
                      dt, (long long)F, (long long)B, tile);
+  P.T_first = first_tile(P.T_out, order, generation, *tdi, dt, P.fir);
   const int64_t rows = channels == LR_XYZ_AET ? 6 : 3;
 
   // grouped forward work list: longest templates first
@@ -104,7 +123,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
                                    order_idx[s]};
       gmax[g] = std::max(gmax[g], T.n_out);
     }
-    tiles1 += (gmax[g] + P.T_out - 1) / P.T_out;
+    tiles1 += (gmax[g] + P.T_first - 1) / P.T_first;
   }
   // Segments of K tiles carry the TDI halo from tile to tile (every tile
   // after the first has `tile` outputs) when the halo fits the kernel's
@@ -115,7 +134,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
   // Every segment starts before its group's longest template ends: the
   // fused kernel relies on it (an item without a tile would skip the barrier
   // that orders the reads of the item index before the next fetch).
-  const int64_t seg_out = P.T_out + (int64_t)(P.K - 1) * tile;
+  const int64_t seg_out = P.T_first + (int64_t)(P.K - 1) * tile;
   for (int64_t g = 0; g < n_groups; ++g) {
     const int64_t segs = (gmax[g] + seg_out - 1) / seg_out;
     for (int64_t sg = 0; sg < segs; ++sg) {
@@ -211,6 +230,9 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
   P.bytes[R_PADJ_SPAN] = adjoint ? P.padj_span.size() * sizeof(int64_t) : 0;
   P.bytes[R_GY] = adjoint ? (size_t)P.gy_doubles * sizeof(double) : 0;
   P.bytes[R_TRIG] = (size_t)n * 4 * sizeof(double);
+  const int64_t n_fir = fir_intervals(P.fir, P.max_n_out);
+  P.bytes[R_FIR] = (size_t)n_fir * fir_table_bytes(P.fir);
+  P.bytes[R_FIR_SPLIT] = (size_t)n_fir * sizeof(int);
   size_t o = 0;
   for (int r = 0; r < R_COUNT; ++r) {
     P.off[r] = o;
@@ -260,8 +282,10 @@ int launch_forward(const lr_batch* b, const double* hp, const double* hc, const 
   a.dt = b->dt;
   a.inv_dt = 1.0 / b->dt;
   a.F = b->front;
-  a.T_out = b->tile_out;
-  a.HP = b->segment > 1 ? b->tile - b->tile_out : 0;
+  lr::FirShape fir;
+  a.T_out = first_tile(b->tile_out, b->order, b->generation, b->tdi, b->dt, fir);
+  a.halo = b->tile - b->tile_out;
+  a.HP = b->segment > 1 ? a.halo : 0;
   a.seg_tiles = b->segment;
   a.hp = hp;
   a.hc = hc;
@@ -271,9 +295,17 @@ int launch_forward(const lr_batch* b, const double* hp, const double* hc, const 
   a.params = params;
   a.channels = b->channels;
   a.out = out;
+  a.n_templates = b->n_templates;
+  a.fir = at<double>(b, R_FIR);
+  a.fir_split = at<int>(b, R_FIR_SPLIT);
+  a.n_fir = (int64_t)((b->off[R_FIR_SPLIT] - b->off[R_FIR]) /
+                      std::max<size_t>(1, fir_table_bytes(fir)));
+  a.fir_lo = fir.lo;
+  a.fir_k = fir.taps;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = lr::run_forward_prep(a.counter, sky, sky_stride, b->n_templates,
-                                      at<double>(b, R_TRIG), s);
+  hipError_t e = hipSuccess;
+  if (fir.taps == 0)
+    e = lr::run_forward_prep(a.counter, sky, sky_stride, b->n_templates, a.trig, s);
   if (e == hipSuccess)
     e = lr::run_fused_forward(b->order, b->generation, b->group, b->tile, params != nullptr, a,
                               b->blocks, s);
@@ -359,7 +391,7 @@ int lr_batch_prepare(const lr_template* t, int64_t n, const lr_orbits* proj,
   for (auto& A : P.adj) A.t_off_h = t_off_p - (double)t[A.index].out_start * dt;
 
   // host image of the workspace, one copy
-  std::vector<char> img(P.total, 0);
+  std::vector<char> img(P.off[R_GY], 0);    // the regions before the link gradient
   auto put = [&](Region r, const void* src) {
     if (P.bytes[r]) std::memcpy(img.data() + P.off[r], src, P.bytes[r]);
   };
@@ -480,8 +512,9 @@ int lr_response_adjoint(const lr_batch* b, const double* hp, const double* hc,
                                       b->n_proj_items, s);
   }
   if (e == hipSuccess && g_sky && b->n_proj_items > 0)
-    e = lr::run_batch_sky_finalize(a.sky_part, at<const int64_t>(b, R_SKY_SPAN), b->n_templates,
-                                   g_sky, s);
+    e = lr::run_batch_sky_finalize(a.sky_part,
+                                   at<const int64_t>(b, R_SKY_SPAN),
+                                   b->n_templates, g_sky, s);
   if (e != hipSuccess)
     return set_error(LR_E_HIP, "lr_response_adjoint launch: %s", hipGetErrorString(e));
   return LR_OK;
@@ -533,7 +566,8 @@ int lr_response_adjoint_gb(const lr_batch* b, const double* params, const double
   }
   if (e == hipSuccess)
     e = lr::run_gb_batch_finalize(a.gb_part, at<const int64_t>(b, R_PADJ_SPAN), a.sky_part,
-                                  at<const int64_t>(b, R_SKY_SPAN), params, b->n_templates,
+                                  at<const int64_t>(b, R_SKY_SPAN),
+                                  params, b->n_templates,
                                   g_params, s);
   if (e != hipSuccess)
     return set_error(LR_E_HIP, "lr_response_adjoint_gb launch: %s", hipGetErrorString(e));

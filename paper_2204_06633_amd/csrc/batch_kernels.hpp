@@ -14,7 +14,7 @@
 #pragma once
 
 #include "batch_types.hpp"
-#include "forward_kernels.hpp"
+#include "fir_tables.hpp"
 
 namespace lr {
 
@@ -137,6 +137,75 @@ __device__ __forceinline__ void fused_tdi(const BatchFwdArgs& a, const double* y
   (void)live;
 }
 
+// The same from the filters: W the lane's position in its interval's table
+// (its DPP row's 16 coefficients), j0 the row element of its first output's
+// first tap, t, u powers of the two outputs' times in the interval.  A weight
+// is computed once and applied to the M templates: 12 K (4 + M) / M
+// instructions per output and template.
+template <int GEN, int M, int YR>
+__device__ __forceinline__ void fused_tdi_fir(const double* ylds, const double2* W, int K, int j0,
+                                              const double (&t)[3], const double (&u)[3],
+                                              double (&acc)[M][2][3]) {
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[m][0][c] = acc[m][1][c] = 0.0;
+  const int NQ = fir_quads(K);
+  // elements j0 + k for even and odd k
+  const double* ev = ylds + par<YR>(j0);
+  const double* od = ylds + par<YR>(j0 + 1);
+  static_for<6>([&](auto L) {
+    constexpr int l = decltype(L)::value;
+    constexpr int c0 = FirTab<GEN>::v.chan[2 * l], c1 = FirTab<GEN>::v.chan[2 * l + 1];
+    double y0[M], y1[M];
+    double2 w = W[0];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      y0[m] = ev[m * 6 * YR];
+      y1[m] = od[m * 6 * YR];
+    }
+    auto pair = [&](double x, int k) {
+      // the link samples of the next taps are read while these are summed
+      double y2[M], z1[M];
+      const int kz = min(k + 1, K / 2 - 1);
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        y2[m] = ev[m * 6 * YR + k + 1];
+        z1[m] = od[m * 6 * YR + kz];
+      }
+      double p[2], r[2];
+      fir_weights<0>(x, t, u, p, r);
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        acc[m][0][c0] = fma(p[0], y0[m], acc[m][0][c0]);
+        acc[m][1][c0] = fma(p[1], y1[m], acc[m][1][c0]);
+        acc[m][0][c1] = fma(r[0], y0[m], acc[m][0][c1]);
+        acc[m][1][c1] = fma(r[1], y1[m], acc[m][1][c1]);
+      }
+      fir_weights<1>(x, t, u, p, r);
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        acc[m][0][c0] = fma(p[0], y1[m], acc[m][0][c0]);
+        acc[m][1][c0] = fma(p[1], y2[m], acc[m][1][c0]);
+        acc[m][0][c1] = fma(r[0], y1[m], acc[m][0][c1]);
+        acc[m][1][c1] = fma(r[1], y2[m], acc[m][1][c1]);
+        y0[m] = y2[m];
+        y1[m] = z1[m];
+      }
+    };
+#pragma unroll 1
+    for (int q = 0; q < NQ; ++q) {
+      const double2 v = W[16 * min(q + 1, NQ - 1)];     // four taps ahead
+      pair(w.x, 2 * q);
+      if (2 * q + 1 < K / 2) pair(w.y, 2 * q + 1);
+      w = v;
+    }
+    W += 16 * NQ;
+    ev += YR;
+    od += YR;
+  });
+}
+
 // Minimum resident waves per SIMD for the fused kernel's register budget
 // (build-time tuning knobs; 1 leaves the compiler unconstrained).  Measured
 // fastest: two for groups of 1 and 4; three for groups of 2 reading h from
@@ -194,10 +263,11 @@ void fused_forward_kernel(BatchFwdArgs a) {
     const int64_t n_long = a.tpl[grp * M].n_out;      // the group's longest template
     // A segment is seg_tiles consecutive tiles.  Row r of a tile holds link
     // sample rb + r (output-index space, rb = first output - F - ro): the
-    // tile's YT new link samples go to rows [hp, hp + YT); from the second
-    // tile on, rows [0, hp) hold the previous tile's last hp samples (rows
-    // [YT, YT + hp) there), so every tile after the first has YT outputs.
+    // tile's new link samples go to rows [hp, hp + YT); from the second
+    // tile on, rows [0, hp) hold the previous tile's last hp samples, so
+    // every tile after the first has YT outputs.
     double halo[NST > 0 ? NST : 1];
+    bool bad = false;                                 // a link sample of the segment is not finite
 #pragma unroll 1
     for (int t = 0; t < a.seg_tiles; ++t) {
       const int64_t o0 = t == 0 ? S : S + a.T_out + (int64_t)(t - 1) * YT;
@@ -222,7 +292,7 @@ void fused_forward_kernel(BatchFwdArgs a) {
         // new rows up to the last valid output's stencil (the padding B
         // rounded to the even halo YT - T_out)
         const int r_end =
-            (int)min((int64_t)YT, n_valid + (YT - a.T_out) - (t == 0 ? 0 : hp));
+            (int)min((int64_t)YT, n_valid + a.halo - (t == 0 ? 0 : hp));
         const int last = r_end - 1;
         const bool act_a = 2 * tid <= last, act_b = 2 * tid + 1 <= last;
         const int ra = act_a ? 2 * tid : (last & ~1);
@@ -248,6 +318,7 @@ void fused_forward_kernel(BatchFwdArgs a) {
           double* row = ylds + (k * 6 + l) * YR;
           if (act_a) row[par<YR>(hp + ra)] = ya[l];
           if (act_b) row[par<YR>(hp + ra + 1)] = yb[l];
+          bad |= !(fabs(ya[l]) <= DBL_MAX && fabs(yb[l]) <= DBL_MAX);
         }
         if (t > 0) {
           // the carried halo of this template back into its rows
@@ -258,17 +329,51 @@ void fused_forward_kernel(BatchFwdArgs a) {
           }
         }
       }
-      __syncthreads();
-
       // 2. TDI of the tile's outputs for all live templates
       const int oa = 2 * tid;                         // tile-relative output of sample a
       const bool out_a = oa < cnt;
       const int ob = out_a ? oa : cnt - 2;            // idle lanes mirror the last pair
-      double La[6], Lb[6];
-      light_times(a.orb_t, a.t_off_t + (double)(o0 + ob) * a.dt, La);
-      light_times(a.orb_t, a.t_off_t + (double)(o0 + ob + 1) * a.dt, Lb);
       double acc[M][2][3];
-      fused_tdi<N, GEN, M, YR>(a, ylds, La, Lb, a.F + ro + ob, live, acc);
+      // The filters' empty taps would spread a NaN or an infinity past the
+      // stencils: such segments interpolate the delays one by one, like the
+      // intervals that no filter serves.
+      bad = __syncthreads_or(bad);
+      bool split = a.fir_k == 0 || bad;
+      if (!split) {
+        // a row of 16 lanes lies in one interval; outputs past the longest
+        // template of the batch have none, and are not stored
+        const int64_t o = o0 + ob;
+        const int qe = (int)a.n_fir - 1, q = min((int)(o / kFirInterval), qe);
+        const int q0 = (int)(o0 / kFirInterval), q1 = min((int)((o0 + cnt - 1) / kFirInterval), qe);
+        const double c = (double)q * kFirInterval + 0.5 * (kFirInterval - 1);
+        constexpr double inv = 2.0 / (kFirInterval - 1);
+        double ta[3], tb[3];
+        ta[0] = ((double)o - c) * inv;
+        tb[0] = ((double)(o + 1) - c) * inv;
+        ta[1] = ta[0] * ta[0];
+        tb[1] = tb[0] * tb[0];
+        ta[2] = ta[1] * ta[0];
+        tb[2] = tb[1] * tb[0];
+        const double2* W = reinterpret_cast<const double2*>(a.fir) +
+                           (int64_t)q * 96 * fir_quads(a.fir_k) + (tid & 15);
+        fused_tdi_fir<GEN, M, YR>(ylds, W, a.fir_k, a.F + a.fir_lo + ro + ob, ta, tb, acc);
+        for (int i = q0; i <= q1; ++i) split |= a.fir_split[i] != 0;
+      }
+      if (split) {                                    // uniform
+        const bool all = a.fir_k == 0 || bad;
+        double La[6], Lb[6], one[M][2][3];
+        light_times(a.orb_t, a.t_off_t + (double)(o0 + ob) * a.dt, La);
+        light_times(a.orb_t, a.t_off_t + (double)(o0 + ob + 1) * a.dt, Lb);
+        fused_tdi<N, GEN, M, YR>(a, ylds, La, Lb, a.F + ro + ob, live, one);
+        const bool mine =
+            all || a.fir_split[min((o0 + ob) / kFirInterval, a.n_fir - 1)] != 0;
+#pragma unroll
+        for (int k = 0; k < M; ++k)
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acc[k][s][c] = mine ? one[k][s][c] : acc[k][s][c];
+      }
 
       // 3. store (the template records read again rather than kept live
       // through the TDI: an opaque copy of the group index stops the compiler
@@ -287,12 +392,13 @@ void fused_forward_kernel(BatchFwdArgs a) {
         }
       }
       if (t + 1 < a.seg_tiles) {
-        // the next tile's halo: this tile's rows [YT, YT + hp), read before
+        // the next tile's halo: this tile's last hp link samples, read before
         // the next tile's projection windows overwrite them
+        const int from = t == 0 ? hp + a.T_out : YT;
 #pragma unroll
         for (int q = 0; q < NST; ++q) {
           const int e = tid + BLOCK * q, rho = e / max(HPX, 1), j = e - rho * HPX;
-          if (rho < M * 6 && j < hp) halo[q] = ylds[rho * YR + par<YR>(YT + j)];
+          if (rho < M * 6 && j < hp) halo[q] = ylds[rho * YR + par<YR>(from + j)];
         }
       }
       __syncthreads();                                // LDS free for the next tile

@@ -27,6 +27,10 @@ constexpr int fused_halo_cap(int m, int block) {
   return c < 32 ? 0 : (c < 64 ? c : 64);
 }
 
+// A table of the TDI filters holds, per link and four taps, 16 pairs: coefficient
+// i of the first two taps and of the last two (fir_tables.hpp).
+constexpr int fir_quads(int taps) { return (taps + 3) / 4; }
+
 struct BatchFwdArgs {
   OrbitView orb_p, orb_t;
   const BatchTemplate* tpl;  // [n_groups * M], grouped, longest template first
@@ -36,17 +40,26 @@ struct BatchFwdArgs {
   double t_off_p, t_off_t;   // time of output sample 0 minus each orbit grid's first sample
   double dt, inv_dt;
   int F;                     // link samples before the first output of a tile
-  int T_out;                 // outputs of a segment's first tile (even): link samples per
-                             // tile minus the TDI halo
-  int HP;                    // halo carried from tile to tile (link samples per tile -
-                             // T_out), 0 for segments of one tile
+  int T_out;                 // outputs of a segment's first tile (even): at most link samples
+                             // per tile minus the TDI halo
+  int halo;                  // TDI halo: padding before and after, rounded up to even
+  int HP;                    // halo carried from tile to tile, 0 for segments of one tile
   int seg_tiles;             // tiles per segment: T_out + (seg_tiles - 1) * link samples per
                              // tile outputs
   const double* hp;
   const double* hc;
   const double* sky;         // lam, beta of template k at sky[sky_stride * k + 0, 1]
   int sky_stride;            // 2 (sky array) or 8 (rows of params)
-  const double* trig;        // [n_templates][4]: sin, cos of lam, then of beta (run_forward_prep)
+  double* trig;              // [n_templates][4]: sin, cos of lam, then of beta
+  int64_t n_templates;
+  // TDI filters, one table per interval of outputs (fir_tables.hpp): taps
+  // o + fir_lo .. + fir_k - 1 of output o; split[q]: interval q needs the
+  // delays interpolated one by one; fir_k 0: all do, and run_forward_prep
+  // fills trig
+  double* fir;               // [n_fir][6 links][fir_quads(fir_k)][16][2]
+  int* fir_split;            // [n_fir]
+  int64_t n_fir;
+  int fir_lo, fir_k;
   const double* params;      // [n_templates][8] or null: synthesise h+ / hx from these
   int channels;
   double* out;
@@ -92,12 +105,15 @@ hipError_t launch_fused_forward(const BatchFwdArgs& a, int blocks, hipStream_t s
 template <int N, int GEN, int M, int BLOCK, bool WAVE>
 int fused_occupancy();
 template <int N, int GEN>
+hipError_t launch_fir_tables(const BatchFwdArgs& a, hipStream_t s);
+template <int N, int GEN>
 hipError_t launch_batch_tdi_adjoint(const BatchAdjArgs& a, int64_t n_items, hipStream_t s);
 template <int N, int GEN>
 hipError_t launch_batch_tdi_fir_adjoint(const BatchAdjArgs& a, int64_t n_items, hipStream_t s);
 template <int N>
 hipError_t launch_batch_project_adjoint(const BatchAdjArgs& a, int64_t n_items,
                                         int64_t n_sky_items, hipStream_t s);
+
 
 // tile: link samples per work item (256, 512 or 1024; not 1024 with group
 // 4); wave: waveform mode (h from a.params; groups 1, 2 at 512 and 2 at 1024)

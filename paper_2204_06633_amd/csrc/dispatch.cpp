@@ -79,8 +79,20 @@ hipError_t run_fused_forward(int order, int gen, int group, int tile, bool wave,
   // the kernel's rows hold at most fused_halo_cap(group, workgroup) carried
   // samples, and a segment of one tile carries none
   if (a.seg_tiles < 1 || a.HP < 0 || a.HP > fused_halo_cap(group, tile / 2) ||
-      (a.seg_tiles > 1) != (a.HP > 0) || (a.HP > 0 && a.HP != tile - a.T_out))
+      (a.seg_tiles > 1) != (a.HP > 0) || (a.HP > 0 && a.HP != a.halo) || a.T_out < 2 ||
+      a.T_out + a.halo > tile || (a.fir_k > 0 && a.T_out % 32 != 0))
     return hipErrorInvalidValue;
+  if (a.fir_k > 0) {
+    hipError_t e = hipErrorInvalidValue;
+    switch (order) {
+#define X(ORD, NT) \
+  case ORD: e = gen == 1 ? launch_fir_tables<NT, 1>(a, s) : launch_fir_tables<NT, 2>(a, s); break;
+      LR_ORDER_CASES(X)
+#undef X
+      default: break;
+    }
+    if (e != hipSuccess) return e;
+  }
   switch (order) {
 #define X(ORD, NT)                                                                        \
   case ORD:                                                                               \
@@ -129,7 +141,9 @@ hipError_t run_batch_tdi_adjoint(int order, int gen, const BatchAdjArgs& a, int6
 hipError_t run_batch_project_adjoint(int order, const BatchAdjArgs& a, int64_t n_items,
                                      int64_t n_sky_items, hipStream_t s) {
   switch (order) {
-#define X(ORD, NT) case ORD: return launch_batch_project_adjoint<NT>(a, n_items, n_sky_items, s);
+#define X(ORD, NT)                                                                        \
+  case ORD:                                                                               \
+    return launch_batch_project_adjoint<NT>(a, n_items, n_sky_items, s);
     LR_ORDER_CASES(X)
 #undef X
     default: return hipErrorInvalidValue;

@@ -101,6 +101,10 @@ struct FirShape {
 FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt, int64_t n,
                        bool adjoint);
 
+// The same for the fused batched forward (any group, so that results do not
+// depend on it).
+FirShape fused_fir_shape(int order, int gen, double L_min, double L_max, double dt);
+
 // Workgroup size of the tiled kernels (output samples per workgroup).
 constexpr int kTile = 256;
 
