@@ -61,6 +61,14 @@ bool fused_variant_exists(int group, int tile, bool wave) {
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
+// Link samples per work item of the projection adjoint.  The workspace call
+// does not see the projection orbits and counts the smallest.
+constexpr int64_t kPadjTileMin = lr::kFarrowRuns * (lr::kFarrowBlock - lr::kFarrowSpread);
+int64_t padj_tile(double L_max, double dt) {
+  const int rows = lr::farrow_rows(L_max, dt);
+  return rows > 0 ? lr::kFarrowRuns * rows : kCarryTile;
+}
+
 // Outputs of a segment's first tile, of at most T_out: whole rows of 16 lanes
 // where the TDI filters serve, since the lanes of a row share a table.
 int first_tile(int T_out, int order, int generation, const lr_orbits& tdi, double dt,
@@ -79,7 +87,8 @@ int64_t fir_intervals(const lr::FirShape& fir, int64_t max_n_out) {
 }
 
 int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, int order,
-              int generation, int channels, int group, int tile, int segment, int adjoint, Plan& P) {
+              int generation, int channels, int group, int tile, int segment, int adjoint,
+              int64_t padj_tile, Plan& P) {
   if (n < 0 || (n > 0 && !t)) return set_error(LR_E_ARG, "bad template list");
   if (group != 1 && group != 2 && group != 4)
     return set_error(LR_E_UNSUPPORTED, "group %d (1, 2 or 4 templates per work item)", group);
@@ -170,7 +179,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
     P.sky_span.push_back((int64_t)P.proj_items.size() / 2 - first);
     P.sky_span.push_back(b);
     const int64_t cfirst = (int64_t)P.padj_citems.size() / 2;
-    for (int64_t tl = 0; tl < (A.n_y + kCarryTile - 1) / kCarryTile; ++tl) {
+    for (int64_t tl = 0; tl < (A.n_y + padj_tile - 1) / padj_tile; ++tl) {
       P.padj_citems.push_back(b);
       P.padj_citems.push_back(tl);
     }
@@ -342,7 +351,8 @@ size_t lr_batch_workspace(const lr_template* t, int64_t n, const lr_orbits* tdi,
                           int order, int generation, int channels, int group, int tile,
                           int segment, int adjoint) {
   Plan P;
-  if (make_plan(t, n, tdi, dt, order, generation, channels, group, tile, segment, adjoint, P))
+  if (make_plan(t, n, tdi, dt, order, generation, channels, group, tile, segment, adjoint,
+                kPadjTileMin, P))
     return 0;
   return P.total;
 }
@@ -356,7 +366,7 @@ int lr_batch_prepare(const lr_template* t, int64_t n, const lr_orbits* proj,
   if (!std::isfinite(t0) || !(dt > 0.0) || !std::isfinite(dt)) return set_error(LR_E_ARG, "bad t0 or dt");
   Plan P;
   if (int st = make_plan(t, n, tdi, dt, order, generation, channels, group, tile, segment,
-                         adjoint, P))
+                         adjoint, padj_tile(proj->L_max, dt), P))
     return st;
   if (!ws || ws_bytes < P.total)
     return set_error(LR_E_WORKSPACE, "workspace %zu bytes < %zu", ws_bytes, P.total);
@@ -503,17 +513,19 @@ int lr_response_adjoint(const lr_batch* b, const double* hp, const double* hc,
   a.sky_stride = 2;
   a.params = nullptr;
   a.gb_part = nullptr;
+  a.rows = lr::farrow_rows(b->proj.L_max, b->dt);
   const int cap_p = lr::carry_row_capacity(b->order, 2.01 * b->proj.L_max, b->dt, 2, 2, 21 * 64);
   if (e == hipSuccess) e = batch_tdi_adjoint(b, a, s);
   if (e == hipSuccess && b->n_proj_items > 0) {
     a.rl_cap = cap_p;
-    a.items = at<const int64_t>(b, cap_p > 0 ? R_PADJ_CITEMS : R_PROJ_ITEMS);
-    e = lr::run_batch_project_adjoint(b->order, a, cap_p > 0 ? b->n_padj_citems : b->n_proj_items,
+    const bool wide = a.rows > 0 || cap_p > 0;
+    a.items = at<const int64_t>(b, wide ? R_PADJ_CITEMS : R_PROJ_ITEMS);
+    e = lr::run_batch_project_adjoint(b->order, a, wide ? b->n_padj_citems : b->n_proj_items,
                                       b->n_proj_items, s);
   }
   if (e == hipSuccess && g_sky && b->n_proj_items > 0)
     e = lr::run_batch_sky_finalize(a.sky_part,
-                                   at<const int64_t>(b, R_SKY_SPAN),
+                                   at<const int64_t>(b, a.rows > 0 ? R_PADJ_SPAN : R_SKY_SPAN),
                                    b->n_templates, g_sky, s);
   if (e != hipSuccess)
     return set_error(LR_E_HIP, "lr_response_adjoint launch: %s", hipGetErrorString(e));
@@ -556,6 +568,7 @@ int lr_response_adjoint_gb(const lr_batch* b, const double* params, const double
   a.g_hc = nullptr;
   a.sky_part = at<double>(b, R_SKY_PART);
   a.gb_part = at<double>(b, R_GB_PART);
+  a.rows = lr::farrow_rows(b->proj.L_max, b->dt);
   a.pairs = at<const int64_t>(b, R_PAIRS);
   a.sky_items = at<const int64_t>(b, R_PROJ_ITEMS);
   hipError_t e = batch_tdi_adjoint(b, a, s);
@@ -566,7 +579,7 @@ int lr_response_adjoint_gb(const lr_batch* b, const double* params, const double
   }
   if (e == hipSuccess)
     e = lr::run_gb_batch_finalize(a.gb_part, at<const int64_t>(b, R_PADJ_SPAN), a.sky_part,
-                                  at<const int64_t>(b, R_SKY_SPAN),
+                                  at<const int64_t>(b, a.rows > 0 ? R_PADJ_SPAN : R_SKY_SPAN),
                                   params, b->n_templates,
                                   g_params, s);
   if (e != hipSuccess)

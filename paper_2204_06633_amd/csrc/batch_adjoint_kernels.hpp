@@ -66,6 +66,7 @@ __device__ __forceinline__ ProjAdjArgs batch_proj_args(const BatchAdjArgs& a,
   x.params = a.params ? a.params + 8 * T.index : nullptr;
   x.k0 = -(T.y_start + a.F);                        // waveform time 0 at output sample 0
   x.gb_part = nullptr;
+  x.rows = 0;
   return x;
 }
 

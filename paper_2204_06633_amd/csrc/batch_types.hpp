@@ -97,6 +97,7 @@ struct BatchAdjArgs {
   const double* params;         // [n][8] or null: waveform mode (see ProjAdjArgs)
   double* gb_part;              // waveform mode: [n_items][7] parameter-gradient sums
   int fir_lo, fir_k;            // TDI filters (see TdiArgs); fir_k 0: scatter kernels
+  int rows;                     // as in ProjAdjArgs
 };
 
 // Launchers (instantiated per tap count in batch_*.hip).
@@ -114,6 +115,8 @@ template <int N>
 hipError_t launch_batch_project_adjoint(const BatchAdjArgs& a, int64_t n_items,
                                         int64_t n_sky_items, hipStream_t s);
 
+template <int N>
+hipError_t launch_batch_farrow_adjoint(const BatchAdjArgs& a, int64_t n_items, hipStream_t s);
 
 // tile: link samples per work item (256, 512 or 1024; not 1024 with group
 // 4); wave: waveform mode (h from a.params; groups 1, 2 at 512 and 2 at 1024)

@@ -22,7 +22,7 @@ TARGET = os.path.join(PKG, "_lisaresp.so")
 # spread evenly over the compile jobs.
 FUSED_UNITS = [(g, nt) for nt in range(2, 33, 2) for g in (1, 2)]
 SOURCES = (["forward_%s.hip" % k for k in "abcd"] + ["adjoint_%s.hip" % k for k in "abcd"] +
-           ["tdifir_%s.hip" % k for k in "abcd"] +
+           ["tdifir_%s.hip" % k for k in "abcd"] + ["farrow_%s.hip" % k for k in "abcd"] +
            ["batchfwd%d_n%d.hip" % u for u in FUSED_UNITS] +
            ["batchadj_%s.hip" % k for k in "abcd"] +
            ["util.hip", "fd_kernels.hip", "gb_kernels.hip", "dispatch.cpp", "api.cpp", "api_batch.cpp",
@@ -34,7 +34,7 @@ def _weight(src):
     """Rough compile cost of a unit (for the job order)."""
     if src.startswith("batchfwd"):
         return 10 + int(src.split("_n")[1][:-4])
-    return 30 if src.startswith(("adjoint", "batchadj", "forward", "tdifir")) else 1
+    return 30 if src.startswith(("adjoint", "batchadj", "forward", "tdifir", "farrow")) else 1
 
 
 def hipcc():
@@ -71,6 +71,58 @@ def _fused_unit(out_dir, name):
     return path
 
 
+def farrow_header(out_dir):
+    """Write farrow_tables.hpp into out_dir: for every tap count N the Lagrange
+    weights as polynomials in u = eps - 1/2 on [-1/2, 1/2], exact rationals
+    rounded once, of degree N - 1 or economised (Chebyshev) to kFarrowDegree.
+    Dropping the higher terms changes an interpolant by at most 2.5e-17 of the
+    largest sample (N = 32; 9e-18 at N = 26)."""
+    from fractions import Fraction as F
+    degree = 15
+    cheb = [[F(1)], [F(0), F(1)]]                     # T_n(x), powers of x
+    for n in range(2, 32):
+        t = [F(0)] + [2 * c for c in cheb[-1]]
+        for i, c in enumerate(cheb[-2]):
+            t[i] -= c
+        cheb.append(t)
+
+    def polynomial(N, i):
+        """Weight of the tap at u = i + 1/2, powers of x = 2 u."""
+        nodes = [F(2 * (k - N // 2) + 1) for k in range(N)]
+        x0, p = F(2 * i + 1), [F(1)]
+        for x in nodes:
+            if x != x0:
+                q = [F(0)] * (len(p) + 1)
+                for k, c in enumerate(p):
+                    q[k + 1] += c / (x0 - x)
+                    q[k] -= c * x / (x0 - x)
+                p = q
+        for n in range(N - 1, degree, -1):            # drop T_n, highest first
+            lead = p[n] / cheb[n][n]
+            p = [c - lead * t for c, t in zip(p, cheb[n])]
+            p.pop(n) if len(p) > n else None
+        return p
+
+    out = ["// Generated by build.py (farrow_header).", "#pragma once", "namespace lr {",
+           "constexpr int kFarrowDegree = %d;" % degree, "template <int N>", "struct FarrowTable;"]
+    for N in range(2, 33, 2):
+        D = min(N - 1, degree)
+        rows = [polynomial(N, i) for i in range(N // 2)]
+        out += ["template <>", "struct FarrowTable<%d> {" % N, "  static constexpr int D = %d;" % D]
+        for name, first in (("e", 0), ("o", 1)):
+            js = range(first, D + 1, 2)
+            out.append("  static constexpr double %s[%d][%d] = {" % (name, len(js), N // 2))
+            for j in js:
+                out.append("      {%s}," % ", ".join(float(r[j] * 2 ** j).hex() for r in rows))
+            out.append("  };")
+        out.append("};")
+    text = "\n".join(out + ["}  // namespace lr", ""])
+    path = os.path.join(out_dir, "farrow_tables.hpp")
+    if not os.path.exists(path) or open(path).read() != text:
+        with open(path, "w") as f:
+            f.write(text)
+
+
 def source_path(src, out_dir):
     if src.startswith("batchfwd"):
         return _fused_unit(out_dir, src)
@@ -83,6 +135,7 @@ def build(verbose=True, jobs=None, target=TARGET, defines=(), out_dir=None):
     for variant libraries built to ``target`` with objects in ``out_dir``."""
     out_dir = out_dir or os.path.join(HERE, "_build")
     os.makedirs(out_dir, exist_ok=True)
+    farrow_header(out_dir)
     cc = hipcc()
     t0 = time.time()
     jobs = jobs or min(os.cpu_count() or 4, int(os.environ.get("MAX_JOBS", "8")), 16)
@@ -93,7 +146,7 @@ def build(verbose=True, jobs=None, target=TARGET, defines=(), out_dir=None):
     while pending or running:
         while pending and len(running) < jobs:
             src, obj = pending.pop(0)
-            cmd = [cc, *flags(), *["-D" + d for d in defines], "-c", source_path(src, out_dir),
+            cmd = [cc, *flags(), "-I" + out_dir, *["-D" + d for d in defines], "-c", source_path(src, out_dir),
                    "-o", obj]
             if verbose:
                 print(" ".join(cmd), flush=True)

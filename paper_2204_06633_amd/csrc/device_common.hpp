@@ -509,6 +509,14 @@ __device__ __forceinline__ double group_delay(const DelayGroup& g, const double 
   return d;
 }
 
+// Tile of workgroup b of n such that each of the 8 XCDs, which take workgroups
+// in turn, works through one run of consecutive tiles: neighbours share orbit
+// segments and window edges, and each XCD has its own L2.
+__device__ __forceinline__ int64_t xcd_tile(unsigned b, unsigned n) {
+  const unsigned x = b & 7, per = n >> 3, more = n & 7;
+  return (int64_t)(x * per + min(x, more) + (b >> 3));
+}
+
 // Wave (64 lanes) and workgroup min / max of an int.
 // ds_swizzle in bit mode: lane i reads lane i ^ X within its 32-lane half
 // (pattern xor_mask << 10 | and_mask 0x1f).  The pattern is an immediate, so

@@ -46,7 +46,8 @@ hipError_t run_tdi_adjoint(int order, int gen, const TdiAdjArgs& a, hipStream_t 
 
 hipError_t run_project_adjoint(int order, const ProjAdjArgs& a, hipStream_t s) {
   switch (order) {
-#define X(ORD, NT) case ORD: return launch_project_adjoint<NT>(a, s);
+#define X(ORD, NT) \
+  case ORD: return a.rows > 0 ? launch_farrow_adjoint<NT>(a, s) : launch_project_adjoint<NT>(a, s);
     LR_ORDER_CASES(X)
 #undef X
     default: return hipErrorInvalidValue;
@@ -143,7 +144,8 @@ hipError_t run_batch_project_adjoint(int order, const BatchAdjArgs& a, int64_t n
   switch (order) {
 #define X(ORD, NT)                                                                        \
   case ORD:                                                                               \
-    return launch_batch_project_adjoint<NT>(a, n_items, n_sky_items, s);
+    return a.rows > 0 ? launch_batch_farrow_adjoint<NT>(a, n_items, s)                    \
+                      : launch_batch_project_adjoint<NT>(a, n_items, n_sky_items, s);
     LR_ORDER_CASES(X)
 #undef X
     default: return hipErrorInvalidValue;

@@ -1,0 +1,9 @@
+// Polynomial projection kernels instantiated for tap counts 2, 4, 6, 8.
+#include "farrow_adjoint.hpp"
+
+namespace lr {
+LR_INSTANTIATE_FARROW_ADJ(2)
+LR_INSTANTIATE_FARROW_ADJ(4)
+LR_INSTANTIATE_FARROW_ADJ(6)
+LR_INSTANTIATE_FARROW_ADJ(8)
+}  // namespace lr

@@ -1,0 +1,444 @@
+// Projection adjoint and sky gradient in one pass (FP64, gfx950): the
+// transpose of the nine interpolations per link sample, and the gradient with
+// respect to the sky angles, from polynomials per stencil base (farrow.hpp).
+//
+// A workgroup of 256 lanes takes two runs of `rows` consecutive link samples,
+// rows = 256 minus the spread of the nine positions, so that 256 stencil bases
+// cover a run.  Per run:
+//   A. lane = link sample: geometry, u and integer part of each position, and
+//      the gradient of each position's h+ and hx, to LDS;
+//   B. lane = stencil base J: coefficients of h+ and hx, then position by
+//      position the link sample r = J - shift it serves: value and derivative
+//      for the sky angles back into r's LDS slots, and the gradients times
+//      powers of u added to J's coefficient gradients; at the end these turn
+//      into the gradients of the N samples around J, summed in the wave's own
+//      LDS row (LDS adds of one wave stay in order), then over the waves, and
+//      added to the zero-filled gradients.  An element receives at most two
+//      additions there, so results are bitwise reproducible.
+//   C. lane = link sample: sky gradient from the values and derivatives.
+//
+// Bound by FP64 issue at two waves per SIMD (registers: 64 coefficients and
+// coefficient gradients per lane).  One year at dt = 10 s, order 25, against
+// nine weight sequences per link sample: with the sky gradient 804 -> 570 us,
+// without 385 -> 313 us.
+#pragma once
+
+#include "batch_adjoint_kernels.hpp"
+#include "farrow.hpp"
+
+namespace lr {
+
+constexpr int kFarrowLd = kFarrowBlock;        // row length of the LDS arrays
+
+// One step of phase B: the link samples whose position `row / kFarrowLd` has
+// integer part f; k = f minus the position's smallest.
+struct FarrowStep {
+  int row, f, k, end;
+};
+constexpr int kFarrowSteps = 48;               // most steps of a run
+
+struct FarrowShared {
+  int lo[9], hi[9];                            // integer parts of the positions in the run
+  alignas(16) FarrowStep step[kFarrowSteps + 3];
+  double s_trig[2][2];
+  double s_part[9][kFarrowBlock / 64];         // per wave: sky gradient, waveform sums
+  gb::Source src;
+  unsigned char f[9 * kFarrowLd];              // integer part minus lo
+};
+
+// Doubles of dynamic LDS: u and the two gradients per position and link
+// sample, the window of h+ and hx, and the waves' sums.
+__host__ __device__ constexpr size_t farrow_adjoint_doubles(int N, bool window) {
+  return 27 * kFarrowLd + (window ? 2 * (kFarrowBlock + N) : 0) + (kFarrowBlock / 64) * 2 * (64 + N);
+}
+
+template <int N, bool SKY, bool WAVE>
+__device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_t tile,
+                                                    double* lds, FarrowShared& sh,
+                                                    double* part_out) {
+  constexpr int H = N / 2, D = FarrowTable<N>::D, LD = kFarrowLd, WR = 64 + N;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  double* U = lds;
+  double* GP = lds + 9 * LD;
+  double* GC = lds + 18 * LD;
+  double2* win = reinterpret_cast<double2*>(lds + 27 * LD);
+  double* sums = lds + 27 * LD + (SKY ? 2 * (kFarrowBlock + N) : 0);
+  double* mine = sums + wv * 2 * WR;
+
+  load_sky(a.sky, sh.s_trig);
+  // the sky basis from its trigonometry in LDS, where it is needed
+  auto trig = [&]() {
+    int i = 0;
+    asm volatile("" : "+v"(i));
+    const double* t = &sh.s_trig[0][0] + i;
+    return SkyTrig{t[0], t[1], t[2], t[3]};
+  };
+  // h+ and hx: the arrays, or the waveform with its constants kept in LDS
+  if (WAVE && tid == 0) sh.src = gb::load_source(a.params);
+  if (lane < 9) sh.s_part[lane][wv] = 0.0;
+  __syncthreads();
+  auto source = [&]() {
+    if constexpr (WAVE) {
+      int i = 0;
+      asm volatile("" : "+v"(i));
+      return HSource::waveform((&sh.src)[i], a.k0, a.dt, a.n_h);
+    } else {
+      return HSource::arrays(a.hp, a.hc, a.n_h);
+    }
+  };
+  // a lane's share of sum `slot`, added over the wave and to the wave's total
+  auto add_up = [&](double v, int slot) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane == 0) sh.s_part[slot][wv] += v;
+  };
+  const int64_t end = min(a.n_y, (tile + 1) * kFarrowRuns * a.rows);
+  int most = a.rows;
+#pragma unroll 1
+  for (int64_t r0 = tile * kFarrowRuns * a.rows; r0 < end;) {
+    int n = (int)min((int64_t)most, end - r0);
+    int t = tid;                               // opaque: nothing hoisted out of the loop
+    asm volatile("" : "+v"(t));
+    const int rel = min(t, n - 1);
+    const bool active = t < n;
+    const int64_t q0 = a.y_start + r0;
+    const double tau = a.t_off + (double)(q0 + rel) * a.dt;
+
+    // A.
+    if (t < 9) {
+      sh.lo[t] = 1 << 30;
+      sh.hi[t] = -(1 << 30);
+    }
+    int lo[9], hi[9];
+    {
+      double gl[6];
+#pragma unroll
+      for (int l = 0; l < 6; ++l) {
+        gl[l] = a.g_y[(int64_t)l * a.n_y + r0 + rel];
+        gl[l] = active ? gl[l] : 0.0;
+      }
+      LinkGeom g;
+      const SkyTrig tr = trig();
+      link_geometry(a.orb, tau, sky_from_trig(tr.sl, tr.cl, tr.sb, tr.cb), g);
+      int f[9], wlo = 0, whi = 0;              // lane p < 9: the wave's range of position p
+      __syncthreads();                         // lo, hi set; the previous run is done with LDS
+#pragma unroll
+      for (int p = 0; p < 9; ++p) {
+        double eps;
+        f[p] = split_delay(position_delay(g, p), a.inv_dt, eps);
+        if (active) U[p * LD + t] = eps - 0.5;
+        const int f0 = __builtin_amdgcn_readfirstlane(f[p]);
+        int x = f0, y = f0;
+        if (!__all(f[p] == f0)) {
+          x = wave_min(f[p]);
+          y = wave_max(f[p]);
+        }
+        wlo = lane == p ? x : wlo;
+        whi = lane == p ? y : whi;
+      }
+      if (lane < 9) {
+        atomicMin(&sh.lo[lane], wlo);
+        atomicMax(&sh.hi[lane], whi);
+      }
+#pragma unroll
+      for (int l = 0; l < 6; ++l) gl[l] /= 2.0 * (1.0 - kDir[l] * g.kn[kArm[l]]);
+      if (active) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          double vp = 0.0, vc = 0.0;
+#pragma unroll
+          for (int l = 0; l < 6; ++l)
+            if (kLinkRecv[l] - 1 == i) {
+              vp = fma(-gl[l], g.xip[kArm[l]], vp);
+              vc = fma(-gl[l], g.xic[kArm[l]], vc);
+            }
+          GP[i * LD + t] = vp;
+          GC[i * LD + t] = vc;
+        }
+#pragma unroll
+        for (int l = 0; l < 6; ++l) {
+          GP[(3 + l) * LD + t] = gl[l] * g.xip[kArm[l]];
+          GC[(3 + l) * LD + t] = gl[l] * g.xic[kArm[l]];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < 9; ++p) {
+        lo[p] = __builtin_amdgcn_readfirstlane(sh.lo[p]);
+        hi[p] = __builtin_amdgcn_readfirstlane(sh.hi[p]);
+        sh.f[p * LD + t] = (unsigned char)(f[p] - lo[p]);
+      }
+    }
+    int jlo = lo[0], jhi = hi[0], drift = 0, steps = 0;
+#pragma unroll
+    for (int p = 0; p < 9; ++p) {
+      jlo = min(jlo, lo[p]);
+      jhi = max(jhi, hi[p]);
+      drift = max(drift, hi[p] - lo[p]);
+      if (t == p && steps + hi[p] - lo[p] < kFarrowSteps)
+        for (int i = 0; i <= hi[p] - lo[p]; ++i)
+          sh.step[steps + i] = FarrowStep{p * LD, lo[p] + i, i, 0};
+      steps += hi[p] - lo[p] + 1;
+    }
+    if (t == 9 && steps <= kFarrowSteps)       // the list's end, and what is read ahead of it
+      sh.step[steps] = sh.step[steps + 1] = sh.step[steps + 2] = FarrowStep{0, 0, 0, 1};
+    // One set of bases for all positions when they lie as close together as
+    // the light times say (the host's `rows`); else one per position, and
+    // fewer link samples where the positions themselves move too fast.
+    const bool together = n + jhi - jlo <= kFarrowBlock;
+    if (n > 1 && (n + drift > kFarrowBlock || steps > kFarrowSteps)) {
+      most = max(1, n / 2);
+      __syncthreads();                         // lo, hi read before they are set again
+      continue;
+    }
+    __syncthreads();                           // f, step
+
+    // B.
+#pragma unroll 1
+    for (int g = 0; g < (together ? 1 : 9); ++g) {
+      int base = jlo, nj = n + jhi - jlo;
+      if (!together) {
+        base = __builtin_amdgcn_readfirstlane(sh.lo[g]);
+        nj = n + __builtin_amdgcn_readfirstlane(sh.hi[g]) - base;
+      }
+      const int64_t j0 = q0 + base - (H - 1);  // h-index of window element 0
+      double cp[D + 1], cc[D + 1], dp[D + 1], dc[D + 1];
+      if constexpr (SKY) {
+        const HSource hs = source();
+        for (int k = t; k < nj + N - 1; k += kFarrowBlock) {
+          int64_t j = j0 + k;
+          j = j < 0 ? 0 : (j > a.n_h - 1 ? a.n_h - 1 : j);
+          win[k] = hs.at(j);
+        }
+        __syncthreads();
+        farrow_coefs<N>(win + min(t, nj - 1), cp, cc);
+      }
+#pragma unroll
+      for (int m = 0; m <= D; ++m) dp[m] = dc[m] = 0.0;
+      for (int e = lane; e < 2 * WR; e += 64) mine[e] = 0.0;
+      // Step by step, each step's LDS reads issued before the previous step's
+      // sums: the link sample r served by this base and its u and gradients,
+      // zero where this base serves none.
+      struct Item {
+        int at;
+        bool ok;
+        double u, gp, gc;
+      };
+      auto fetch = [&](const FarrowStep& st) {
+        Item it;
+        const int r = t + base - st.f, rc = min(max(r, 0), n - 1);
+        it.at = st.row + rc;
+        it.ok = r == rc && (int)sh.f[it.at] == st.k;
+        it.u = U[it.at];
+        it.gp = GP[it.at];
+        it.gc = GC[it.at];
+        return it;
+      };
+      auto uniform = [](const FarrowStep& v) {
+        return FarrowStep{__builtin_amdgcn_readfirstlane(v.row), __builtin_amdgcn_readfirstlane(v.f),
+                          __builtin_amdgcn_readfirstlane(v.k),
+                          __builtin_amdgcn_readfirstlane(v.end)};
+      };
+      int i = 0;
+      if (!together)
+        while (__builtin_amdgcn_readfirstlane(sh.step[i].row) != g * LD) ++i;
+      Item it = fetch(uniform(sh.step[i]));
+      FarrowStep nxt = uniform(sh.step[i + 1]), later = sh.step[i + 2];
+      i += 2;
+#pragma unroll 1
+      for (;;) {
+        const Item ahead = fetch(nxt);
+        const bool last = nxt.end || (!together && nxt.row != g * LD);
+        nxt = uniform(later);
+        later = sh.step[min(++i, kFarrowSteps + 2)];
+        const double u = it.ok ? it.u : 0.0;
+        const double gp = it.ok ? it.gp : 0.0, gc = it.ok ? it.gc : 0.0;
+        if constexpr (SKY) {
+          double vp = cp[D], vc = cc[D], wp = cp[D], wc = cc[D];   // w: derivative
+#pragma unroll
+          for (int m = D - 1; m >= 0; --m) {
+            vp = fma(vp, u, cp[m]);
+            vc = fma(vc, u, cc[m]);
+            if (m > 0) {
+              wp = fma(wp, u, vp);
+              wc = fma(wc, u, vc);
+            }
+          }
+          if (it.ok) {
+            U[it.at] = fma(gp, wp, gc * wc);
+            GP[it.at] = vp;
+            GC[it.at] = vc;
+          }
+        }
+        dp[0] += gp;
+        dc[0] += gc;
+        double pw = u;
+#pragma unroll
+        for (int m = 1; m <= D; ++m) {
+          dp[m] = fma(gp, pw, dp[m]);
+          dc[m] = fma(gc, pw, dc[m]);
+          if (m < D) pw *= u;
+        }
+        it = ahead;
+        if (last) break;
+      }
+      // coefficient gradients -> gradients of the samples j0 + t + k, added to
+      // the wave's own sums tap after tap (LDS adds of one wave keep their
+      // order)
+      farrow_transpose<N>(dp, dc, [&](int k, double gp, double gc) {
+        unsafeAtomicAdd(mine + lane + k, gp);
+        unsafeAtomicAdd(mine + WR + lane + k, gc);
+      });
+      __syncthreads();
+      double acc[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+      const HSource hs = source();
+      for (int e = t; e < nj + N - 1; e += kFarrowBlock) {
+        double v[2] = {0.0, 0.0};
+#pragma unroll
+        for (int w = 0; w < kFarrowBlock / 64; ++w) {
+          const int i = e - 64 * w;
+          if (i >= 0 && i < WR - 1) {
+            v[0] += sums[w * 2 * WR + i];
+            v[1] += sums[w * 2 * WR + WR + i];
+          }
+        }
+        const int64_t j = j0 + e;
+        if (j >= 0 && j < a.n_h) {
+          if constexpr (WAVE) {
+            gb::adjoint_sums(hs.src, (double)(a.k0 + j) * a.dt, v[0], v[1], acc);
+          } else {
+            atomicAdd(a.g_hp + j, v[0]);
+            atomicAdd(a.g_hc + j, v[1]);
+          }
+        }
+      }
+      if constexpr (WAVE) {
+#pragma unroll
+        for (int k = 0; k < 7; ++k) add_up(acc[k], 2 + k);
+      }
+      if (!together) __syncthreads();          // the next position's window and sums
+    }
+
+    // C.
+    if constexpr (SKY) {
+      const double inv_cdt = a.inv_dt / kC;
+      LinkGeom g;
+      const SkyTrig tr = trig();
+      int rc = rel;
+      asm volatile("" : "+v"(rc));             // read and computed again, not kept through B
+      double gy[6];
+#pragma unroll
+      for (int l = 0; l < 6; ++l) gy[l] = a.g_y[(int64_t)l * a.n_y + r0 + rc];
+      link_geometry(a.orb, a.t_off + (double)(q0 + rc) * a.dt,
+                    sky_from_trig(tr.sl, tr.cl, tr.sb, tr.cb), g);
+      // the derivatives along each spacecraft's delay
+      double s[3], Gk[3], Gu[3] = {0.0, 0.0, 0.0}, Gv[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < 3; ++i) s[i] = U[i * LD + rel];
+#pragma unroll
+      for (int l = 0; l < 6; ++l) s[kLinkEmit[l] - 1] += U[(3 + l) * LD + rel];
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        Gk[c] = -inv_cdt * (s[0] * g.x[0][c] + s[1] * g.x[1][c] + s[2] * g.x[2][c]);
+#pragma unroll
+      for (int l = 0; l < 6; ++l) {
+        const int arm = kArm[l], r = kLinkRecv[l] - 1;
+        const double hp = GP[(3 + l) * LD + rel] - GP[r * LD + rel];
+        const double hc = GC[(3 + l) * LD + rel] - GC[r * LD + rel];
+        const double inv = 1.0 / (1.0 - kDir[l] * g.kn[arm]);
+        const double gl = 0.5 * gy[l] * inv;
+        const double sn = gl * inv * kDir[l] * (g.xip[arm] * hp + g.xic[arm] * hc);
+        const double su = 2.0 * gl * (g.un[arm] * hp + g.vn[arm] * hc);
+        const double sv = 2.0 * gl * (g.un[arm] * hc - g.vn[arm] * hp);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          Gk[c] = fma(sn, g.n[arm][c], Gk[c]);
+          Gu[c] = fma(su, g.n[arm][c], Gu[c]);
+          Gv[c] = fma(sv, g.n[arm][c], Gv[c]);
+        }
+      }
+      const SkyDeriv sd = sky_derivatives(tr.sl, tr.cl, tr.sb, tr.cb);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        double v = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          v += Gk[c] * sd.dk[i][c] + Gu[c] * sd.du[i][c] + Gv[c] * sd.dv[i][c];
+        add_up(active ? v : 0.0, i);
+      }
+    }
+    r0 += n;
+  }
+
+  // the waves' totals in wave order
+  if constexpr (SKY || WAVE) {
+    __syncthreads();
+    if (tid < 9) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < kFarrowBlock / 64; ++w) v += sh.s_part[tid][w];
+      if (SKY && tid < 2) part_out[tid] = v;
+      if (WAVE && tid >= 2) a.gb_part[tid - 2] = v;
+    }
+  }
+}
+
+template <int N, bool SKY>
+__global__ __launch_bounds__(kFarrowBlock, 2) void farrow_adjoint_kernel(ProjAdjArgs a) {
+  extern __shared__ double lds_dyn[];
+  __shared__ FarrowShared sh;
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  farrow_adjoint_tile<N, SKY, false>(a, tile, lds_dyn, sh, a.sky_part + 2 * tile);
+}
+
+template <int N, bool SKY, bool WAVE>
+__global__ __launch_bounds__(kFarrowBlock, 2) void batch_farrow_adjoint_kernel(BatchAdjArgs a) {
+  extern __shared__ double lds_dyn[];
+  __shared__ FarrowShared sh;
+  const int64_t item = xcd_tile(blockIdx.x, gridDim.x);
+  const int64_t b = a.items[2 * item], tile = a.items[2 * item + 1];
+  ProjAdjArgs x = batch_proj_args(a, a.tpl[b]);
+  x.rows = a.rows;
+  if (WAVE) x.gb_part = a.gb_part + 7 * item;
+  farrow_adjoint_tile<N, SKY, WAVE>(x, tile, lds_dyn, sh, a.sky_part + 2 * item);
+}
+
+template <int N>
+hipError_t launch_farrow_adjoint(const ProjAdjArgs& a, hipStream_t s) {
+  const int64_t blocks = (a.n_y + kFarrowRuns * a.rows - 1) / (kFarrowRuns * a.rows);
+  const bool sky = a.sky_part != nullptr;
+  const size_t bytes = farrow_adjoint_doubles(N, sky) * sizeof(double);
+  if (sky) {
+    const hipError_t e = allow_dynamic_lds(farrow_adjoint_kernel<N, true>, bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((farrow_adjoint_kernel<N, true>), dim3((unsigned)blocks), dim3(kFarrowBlock),
+                       bytes, s, a);
+  } else {
+    hipLaunchKernelGGL((farrow_adjoint_kernel<N, false>), dim3((unsigned)blocks), dim3(kFarrowBlock),
+                       bytes, s, a);
+  }
+  return hipGetLastError();
+}
+
+template <int N>
+hipError_t launch_batch_farrow_adjoint(const BatchAdjArgs& a, int64_t n_items, hipStream_t s) {
+  const bool sky = a.sky_part != nullptr;
+  const size_t bytes = farrow_adjoint_doubles(N, sky) * sizeof(double);
+  const dim3 grid((unsigned)n_items), block(kFarrowBlock);
+  hipError_t e = allow_dynamic_lds(batch_farrow_adjoint_kernel<N, true, true>, bytes);
+  if (e == hipSuccess) e = allow_dynamic_lds(batch_farrow_adjoint_kernel<N, true, false>, bytes);
+  if (e != hipSuccess) return e;
+  if (a.params)
+    hipLaunchKernelGGL((batch_farrow_adjoint_kernel<N, true, true>), grid, block, bytes, s, a);
+  else if (sky)
+    hipLaunchKernelGGL((batch_farrow_adjoint_kernel<N, true, false>), grid, block, bytes, s, a);
+  else
+    hipLaunchKernelGGL((batch_farrow_adjoint_kernel<N, false, false>), grid, block, bytes, s, a);
+  return hipGetLastError();
+}
+
+#define LR_INSTANTIATE_FARROW_ADJ(NT)                                                       \
+  template hipError_t launch_farrow_adjoint<NT>(const ProjAdjArgs&, hipStream_t);           \
+  template hipError_t launch_batch_farrow_adjoint<NT>(const BatchAdjArgs&, int64_t, hipStream_t);
+
+}  // namespace lr

@@ -1,0 +1,9 @@
+// Polynomial projection kernels instantiated for tap counts 18, 20, 22, 24.
+#include "farrow_adjoint.hpp"
+
+namespace lr {
+LR_INSTANTIATE_FARROW_ADJ(18)
+LR_INSTANTIATE_FARROW_ADJ(20)
+LR_INSTANTIATE_FARROW_ADJ(22)
+LR_INSTANTIATE_FARROW_ADJ(24)
+}  // namespace lr

@@ -1,0 +1,9 @@
+// Polynomial projection kernels instantiated for tap counts 26, 28, 30, 32.
+#include "farrow_adjoint.hpp"
+
+namespace lr {
+LR_INSTANTIATE_FARROW_ADJ(26)
+LR_INSTANTIATE_FARROW_ADJ(28)
+LR_INSTANTIATE_FARROW_ADJ(30)
+LR_INSTANTIATE_FARROW_ADJ(32)
+}  // namespace lr

@@ -167,11 +167,15 @@ struct HSource {
   // params: A, f0, fdot, phi0, iota, psi (lam, beta unused here)
   __device__ __forceinline__ static HSource waveform(const double* params, int64_t k0, double dt,
                                                      int64_t n_h) {
+    return waveform(gb::load_source(params), k0, dt, n_h);
+  }
+  __device__ __forceinline__ static HSource waveform(const gb::Source& src, int64_t k0, double dt,
+                                                     int64_t n_h) {
     HSource h;
     h.hp = h.hc = nullptr;
     h.n_h = n_h;
     h.wave = true;
-    h.src = gb::load_source(params);
+    h.src = src;
     h.ap0 = -(1.0 + h.src.ci * h.src.ci) * h.src.A;
     h.ac0 = -2.0 * h.src.ci * h.src.A;
     h.dt = dt;

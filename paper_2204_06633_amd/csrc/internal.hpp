@@ -67,6 +67,7 @@ struct ProjAdjArgs {
   const double* params;
   int64_t k0;
   double* gb_part;
+  int rows;             // link samples per run of the polynomial kernel; 0: the other kernels
 };
 
 // Per-tap-count launchers (N = order + 1), instantiated in forward_*.hip.
@@ -83,6 +84,8 @@ template <int N>
 hipError_t launch_tdi_adjoint(const TdiAdjArgs& a, int gen, hipStream_t s);
 template <int N>
 hipError_t launch_project_adjoint(const ProjAdjArgs& a, hipStream_t s);
+template <int N>
+hipError_t launch_farrow_adjoint(const ProjAdjArgs& a, hipStream_t s);
 
 // Records a formatted message for lr_last_error() and returns `status`.
 int set_error(int status, const char* fmt, ...);
@@ -104,6 +107,12 @@ FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt
 // The same for the fused batched forward (any group, so that results do not
 // depend on it).
 FirShape fused_fir_shape(int order, int gen, double L_min, double L_max, double dt);
+
+// Polynomial projection kernels (farrow.hpp): lanes of a workgroup, runs of link
+// samples per workgroup, and link samples per run, or 0 where the nine
+// positions lie too far apart for them.
+constexpr int kFarrowBlock = 256, kFarrowRuns = 2, kFarrowSpread = 64;
+int farrow_rows(double L_max, double dt);
 
 // Workgroup size of the tiled kernels (output samples per workgroup).
 constexpr int kTile = 256;

@@ -16,7 +16,7 @@ __global__ __launch_bounds__(kBlock, 4) void tdi_fir_kernel(TdiArgs a) {
   __shared__ FirShared sh;
   const int tid = threadIdx.x, K = a.fir_k, lo = a.fir_lo, half = (kFwdTile + K) / 2;
   double* W = lds_dyn + 12 * half;
-  const int64_t i0 = (int64_t)blockIdx.x * kFwdTile;
+  const int64_t i0 = xcd_tile(blockIdx.x, gridDim.x) * kFwdTile;
   const int cnt = (int)min((int64_t)kFwdTile, a.n_out - i0);
   const int64_t base = a.out_start + i0 + lo, ymax = a.n_y - 1;
   FirLane f;
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kBlock, 4) void tdi_fir_adjoint_kernel(TdiAdjArgs a
   __shared__ FirShared sh;
   const TdiAdjArgs x[1] = {a};
   const bool live[1] = {true};
-  tdi_fir_adjoint_tile<N, GEN, 1>(x, live, blockIdx.x, lds_dyn, sh);
+  tdi_fir_adjoint_tile<N, GEN, 1>(x, live, xcd_tile(blockIdx.x, gridDim.x), lds_dyn, sh);
 }
 
 template <int N, int GEN>
@@ -246,7 +246,7 @@ template <int N, int GEN>
 __global__ __launch_bounds__(kBlock, 4) void batch_tdi_fir_adjoint_kernel(BatchAdjArgs a) {
   extern __shared__ double lds_dyn[];
   __shared__ FirShared sh;
-  const int64_t item = blockIdx.x;
+  const int64_t item = xcd_tile(blockIdx.x, gridDim.x);
   const int64_t pr = a.items[2 * item], tile = a.items[2 * item + 1];
   const int64_t b0 = a.pairs[2 * pr], b1 = a.pairs[2 * pr + 1];
   TdiAdjArgs x[2] = {batch_tdi_args(a, a.tpl[b0]), batch_tdi_args(a, a.tpl[b1 >= 0 ? b1 : b0])};
