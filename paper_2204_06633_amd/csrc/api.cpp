@@ -53,15 +53,15 @@ int carry_row_capacity(int order, double spread, double dt, int rows, int ncarry
 // forward 232 against 535, adjoint 260 against 842; generation 1 forward 202
 // against 254; 32,768 samples of generation 2 20.8 against 40.8.  At dt = 2 s
 // the taps outgrow N and low orders and generation 1 stay with the streams.
-static FirShape fir_taps(int order, int gen, double L_min, double L_max, double dt) {
+static FirShape fir_taps(int order, int gen, double L_min, double L_max, double dt, double most) {
   const double s = std::ceil((gen == 1 ? 3 : 7) * L_max / dt);
-  if (!(L_min > 0.0) || !(s < 40.0)) return {0, 0};
+  if (!(L_min > 0.0) || !(s < most)) return {0, 0};
   return {-(int)s - ((order + 1) / 2 - 1), (order + (int)s + 1) & ~1};
 }
 
 FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt, int64_t n,
                        bool adjoint) {
-  const FirShape f = fir_taps(order, gen, L_min, L_max, dt);
+  const FirShape f = fir_taps(order, gen, L_min, L_max, dt, 40.0);
   // {intercept, slope}: filters, one by one in generation 1 and 2
   constexpr double fwd[2][6] = {{8.5, 0.38, 12.0, 0.31, 20.0, 0.68},
                                 {33.0, 6.2, 66.0, 7.4, 85.0, 17.6}};
@@ -72,18 +72,21 @@ FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt
   return f;
 }
 
-int farrow_rows(double L_max, double dt) {
+int farrow_rows(double L_max, double dt, int lanes, int most) {
   // the positions of a physical constellation lie within 2.01 light times
   const double s = std::ceil(2.01 * L_max / dt) + 2.0;
-  return s >= 2.0 && s <= kFarrowSpread ? kFarrowBlock - (int)s : 0;
+  return s >= 2.0 && s <= most ? lanes - (int)s : lanes;
 }
 
 // The fused forward shares a filter weight between the templates of a work item
 // (operations per output and template in groups of two: 36 per tap, against
-// 129 N one by one in generation 2 and 55 N in generation 1).  Order 25 at
-// dt = 10 s, 32 templates of 1.5 million outputs: 9.88 -> 6.40 ms.
+// 129 N one by one in generation 2 and 55 N in generation 1).  Order 25, 32
+// templates: 1.5 million outputs at dt = 10 s 9.88 -> 6.40 ms; 200,000 outputs
+// at dt = 1.5 s 1.67 against 1.34 ms, at 1 s 1.77 against 1.68, at 0.7 s 1.82
+// against 1.98, where the rule takes one by one.  Its tables need LDS only
+// while they are built: 120 samples of delay keep that below 64 KB.
 FirShape fused_fir_shape(int order, int gen, double L_min, double L_max, double dt) {
-  const FirShape f = fir_taps(order, gen, L_min, L_max, dt);
+  const FirShape f = fir_taps(order, gen, L_min, L_max, dt, 120.0);
   const int N = order + 1;
   if (36.0 * f.taps + 150.0 > (gen == 1 ? 55.0 * N + 170.0 : 129.0 * N + 400.0)) return {0, 0};
   return f;
@@ -407,6 +410,13 @@ int lr_project_links(const lr_orbits* orb, double t0_h, double dt, int64_t n_h, 
   a.y_start = y_start;
   a.n_y = n_y;
   a.y = y;
+  // positions too far apart for a workgroup's bases (dt below 0.1 s): a full
+  // workgroup, which reads each stencil from h
+  a.rows = lr::farrow_rows(orb->L_max, dt, lr::kFarrowBlock, lr::kFarrowBlock - 64);
+  // two runs per workgroup pay for its start only when every CU has many (order
+  // 25, dt = 10 s, one and two runs: 8640 samples 13.2 and 17.5 us, 400,000
+  // 31.3 and 36.7 us, 3,155,760 183 and 173 us)
+  a.runs = n_y > 500000 ? lr::kFarrowRuns : 1;
   hipError_t e = lr::run_project_links(order, a, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "lr_project_links launch");
   return LR_OK;
@@ -542,7 +552,7 @@ int lr_project_adjoint(const lr_orbits* orb, double t0_h, double dt, int64_t n_h
   // (3,155,760 samples at dt = 10 s: order 7 236 against 247 us, order 13 277
   // against 276, order 25 385 against 313); with it the polynomials always are
   // (order 1 368 against 324, order 25 804 against 570).
-  a.rows = g_sky || order >= 15 ? lr::farrow_rows(orb->L_max, dt) : 0;
+  a.rows = g_sky || order >= 15 ? lr::farrow_adjoint_rows(orb->L_max, dt) : 0;
   e = lr::run_project_adjoint(order, a, s);
   const int64_t tile = a.rows > 0 ? lr::kFarrowRuns * a.rows : lr::kTile;      // link samples per partial sum
   if (e == hipSuccess && g_sky)

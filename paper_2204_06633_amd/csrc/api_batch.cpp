@@ -42,6 +42,7 @@ struct Plan {
   std::vector<lr::BatchAdjTemplate> adj;
   std::vector<int64_t> tdi_items, proj_items, sky_span, like_items, like_span, pairs;
   std::vector<int64_t> tdi_citems, padj_citems, padj_span;
+  int64_t padj_most = 0;                // room for padj_citems at kPadjTileMin
   int64_t gy_doubles = 0, h_extent = 0, out_extent = 0, max_n_out = 0;
   size_t bytes[R_COUNT] = {};
   size_t off[R_COUNT] = {};
@@ -62,20 +63,45 @@ bool fused_variant_exists(int group, int tile, bool wave) {
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // Link samples per work item of the projection adjoint.  The workspace call
-// does not see the projection orbits and counts the smallest.
+// does not see the projection orbits: the workspace holds items of the
+// smallest.
 constexpr int64_t kPadjTileMin = lr::kFarrowRuns * (lr::kFarrowBlock - lr::kFarrowSpread);
 int64_t padj_tile(double L_max, double dt) {
-  const int rows = lr::farrow_rows(L_max, dt);
+  const int rows = lr::farrow_adjoint_rows(L_max, dt);
   return rows > 0 ? lr::kFarrowRuns * rows : kCarryTile;
 }
 
-// Outputs of a segment's first tile, of at most T_out: whole rows of 16 lanes
-// where the TDI filters serve, since the lanes of a row share a table.
-int first_tile(int T_out, int order, int generation, const lr_orbits& tdi, double dt,
-               lr::FirShape& fir) {
-  fir = lr::fused_fir_shape(order, generation, tdi.L_min, tdi.L_max, dt);
-  if (T_out < 32) fir = {0, 0};
-  return fir.taps > 0 ? T_out & ~31 : T_out;
+// The fused kernel's tiles: link samples per run of the projection and per
+// tile, outputs of a segment's first tile, TDI filters.
+struct FusedTile {
+  int rows, samples, first;
+  lr::FirShape fir;
+};
+FusedTile fused_tile(int tile, int halo, int order, int generation, const lr_orbits& tdi,
+                     double dt) {
+  FusedTile f;
+  const int lanes = tile / 2;
+  // A run is a workgroup's lanes minus the spread of the nine positions (2.01
+  // light times; the projection's orbits may have a quarter longer ones than
+  // the delays' before a run falls back to single stencils), in eights so that
+  // a tile of two runs is whole rows of 16 lanes of output pairs.  Where that
+  // leaves a tile too few outputs next to its halo (dt below about 1 s), it
+  // takes more and emptier runs (32 templates of 200,000 outputs, order 25, dt =
+  // 0.5 s: 2375 us in two runs, 2069 in three); beyond that the runs read single
+  // stencils.
+  f.rows = lr::farrow_rows(1.25 * tdi.L_max, dt, lanes, lanes - 64);
+  f.samples = tile;
+  if (f.rows < lanes) {
+    f.rows = std::min(f.rows & ~7, lanes - 8);
+    if (8 * (2 * f.rows - halo) >= 7 * (tile - halo)) f.samples = 2 * f.rows;
+  }
+  // whole rows of 16 lanes where the filters serve: the lanes of a row share a
+  // table
+  f.fir = lr::fused_fir_shape(order, generation, tdi.L_min, tdi.L_max, dt);
+  f.first = f.samples - halo;
+  if (f.first < 32) f.fir = {0, 0};
+  if (f.fir.taps > 0) f.first &= ~31;
+  return f;
 }
 
 size_t fir_table_bytes(const lr::FirShape& fir) {
@@ -111,7 +137,9 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
     return set_error(LR_E_UNSUPPORTED, "dt = %g s is too small for the fused kernel (the TDI "
                                        "stencil needs %lld + %lld of %d link samples)",
                      dt, (long long)F, (long long)B, tile);
-  P.T_first = first_tile(P.T_out, order, generation, *tdi, dt, P.fir);
+  const FusedTile ft = fused_tile(tile, tile - P.T_out, order, generation, *tdi, dt);
+  P.T_first = ft.first;
+  P.fir = ft.fir;
   const int64_t rows = channels == LR_XYZ_AET ? 6 : 3;
 
   // grouped forward work list: longest templates first
@@ -135,7 +163,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
     tiles1 += (gmax[g] + P.T_first - 1) / P.T_first;
   }
   // Segments of K tiles carry the TDI halo from tile to tile (every tile
-  // after the first has `tile` outputs) when the halo fits the kernel's
+  // after the first has as many outputs as link samples) when the halo fits the kernel's
   // rows; automatic K: up to 8 while the batch keeps >= 2048 work items.
   if (tile - P.T_out > lr::fused_halo_cap(group, tile / 2)) P.K = 1;   // workgroup: tile / 2
   else if (segment > 0) P.K = segment;
@@ -143,7 +171,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
   // Every segment starts before its group's longest template ends: the
   // fused kernel relies on it (an item without a tile would skip the barrier
   // that orders the reads of the item index before the next fetch).
-  const int64_t seg_out = P.T_first + (int64_t)(P.K - 1) * tile;
+  const int64_t seg_out = P.T_first + (int64_t)(P.K - 1) * ft.samples;
   for (int64_t g = 0; g < n_groups; ++g) {
     const int64_t segs = (gmax[g] + seg_out - 1) / seg_out;
     for (int64_t sg = 0; sg < segs; ++sg) {
@@ -178,6 +206,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
     P.sky_span.push_back(first);
     P.sky_span.push_back((int64_t)P.proj_items.size() / 2 - first);
     P.sky_span.push_back(b);
+    P.padj_most += (A.n_y + kPadjTileMin - 1) / kPadjTileMin;
     const int64_t cfirst = (int64_t)P.padj_citems.size() / 2;
     for (int64_t tl = 0; tl < (A.n_y + padj_tile - 1) / padj_tile; ++tl) {
       P.padj_citems.push_back(b);
@@ -234,8 +263,8 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
   P.bytes[R_LIKE_SPAN] = P.like_span.size() * sizeof(int64_t);
   P.bytes[R_PAIRS] = adjoint ? P.pairs.size() * sizeof(int64_t) : 0;
   P.bytes[R_TDI_CITEMS] = adjoint ? P.tdi_citems.size() * sizeof(int64_t) : 0;
-  P.bytes[R_PADJ_CITEMS] = adjoint ? P.padj_citems.size() * sizeof(int64_t) : 0;
-  P.bytes[R_GB_PART] = adjoint ? P.padj_citems.size() / 2 * 7 * sizeof(double) : 0;
+  P.bytes[R_PADJ_CITEMS] = adjoint ? (size_t)P.padj_most * 2 * sizeof(int64_t) : 0;
+  P.bytes[R_GB_PART] = adjoint ? (size_t)P.padj_most * 7 * sizeof(double) : 0;
   P.bytes[R_PADJ_SPAN] = adjoint ? P.padj_span.size() * sizeof(int64_t) : 0;
   P.bytes[R_GY] = adjoint ? (size_t)P.gy_doubles * sizeof(double) : 0;
   P.bytes[R_TRIG] = (size_t)n * 4 * sizeof(double);
@@ -291,9 +320,12 @@ int launch_forward(const lr_batch* b, const double* hp, const double* hc, const 
   a.dt = b->dt;
   a.inv_dt = 1.0 / b->dt;
   a.F = b->front;
-  lr::FirShape fir;
-  a.T_out = first_tile(b->tile_out, b->order, b->generation, b->tdi, b->dt, fir);
   a.halo = b->tile - b->tile_out;
+  const FusedTile ft = fused_tile(b->tile, a.halo, b->order, b->generation, b->tdi, b->dt);
+  const lr::FirShape& fir = ft.fir;
+  a.rows = ft.rows;
+  a.samples = ft.samples;
+  a.T_out = ft.first;
   a.HP = b->segment > 1 ? a.halo : 0;
   a.seg_tiles = b->segment;
   a.hp = hp;
@@ -513,7 +545,7 @@ int lr_response_adjoint(const lr_batch* b, const double* hp, const double* hc,
   a.sky_stride = 2;
   a.params = nullptr;
   a.gb_part = nullptr;
-  a.rows = lr::farrow_rows(b->proj.L_max, b->dt);
+  a.rows = lr::farrow_adjoint_rows(b->proj.L_max, b->dt);
   const int cap_p = lr::carry_row_capacity(b->order, 2.01 * b->proj.L_max, b->dt, 2, 2, 21 * 64);
   if (e == hipSuccess) e = batch_tdi_adjoint(b, a, s);
   if (e == hipSuccess && b->n_proj_items > 0) {
@@ -568,7 +600,7 @@ int lr_response_adjoint_gb(const lr_batch* b, const double* params, const double
   a.g_hc = nullptr;
   a.sky_part = at<double>(b, R_SKY_PART);
   a.gb_part = at<double>(b, R_GB_PART);
-  a.rows = lr::farrow_rows(b->proj.L_max, b->dt);
+  a.rows = lr::farrow_adjoint_rows(b->proj.L_max, b->dt);
   a.pairs = at<const int64_t>(b, R_PAIRS);
   a.sky_items = at<const int64_t>(b, R_PROJ_ITEMS);
   hipError_t e = batch_tdi_adjoint(b, a, s);

@@ -5,15 +5,17 @@
 // takes work items (a group of M templates, a tile of output samples) from an
 // atomic counter until the list is exhausted.  For one item it
 //   1. computes, template by template, the link series of the tile plus the
-//      TDI halo directly into LDS (projection, Sec. IV.B) -- the link series
-//      never reaches HBM;
+//      TDI halo directly into LDS (projection, Sec. IV.B, farrow_forward.hpp)
+//      -- the link series never reaches HBM;
 //   2. evaluates TDI (Sec. IV.C) for all M templates at once: the delays
-//      depend on the orbits only, so each Lagrange coefficient sequence is
-//      generated once per sample and applied to the M templates' series;
+//      depend on the orbits only, so each filter weight (fir_tables.hpp), or
+//      each Lagrange coefficient sequence where the filters do not serve, is
+//      formed once per sample and applied to the M templates' series;
 //   3. stores X/Y/Z and/or A/E/T of each template.
 #pragma once
 
 #include "batch_types.hpp"
+#include "farrow_forward.hpp"
 #include "fir_tables.hpp"
 
 namespace lr {
@@ -207,42 +209,26 @@ __device__ __forceinline__ void fused_tdi_fir(const double* ylds, const double2*
 }
 
 // Minimum resident waves per SIMD for the fused kernel's register budget
-// (build-time tuning knobs; 1 leaves the compiler unconstrained).  Measured
-// fastest: two for groups of 1 and 4; three for groups of 2 reading h from
-// HBM (whose 49 KB of LDS let three work-groups share a CU; 203 against 206
-// ms on the 512-template batch although the third wave costs some spills);
-// two for groups of 2 in waveform mode (the synthesis needs more registers:
-// 114 against 125 ms on 256 one-year walkers).
+// (build-time tuning knob).  Two: LDS lets no more workgroups of the usual
+// shapes share a CU, and the projection's coefficients need the registers.
 #ifndef LR_FUSED_MIN_WAVES
 #define LR_FUSED_MIN_WAVES 2
-#endif
-#ifndef LR_FUSED2_MIN_WAVES
-#define LR_FUSED2_MIN_WAVES 3
-#endif
-#ifndef LR_FUSED2W_MIN_WAVES
-#define LR_FUSED2W_MIN_WAVES 2
 #endif
 
 // WAVE: h+ / hx synthesised from each template's parameter row (Sec. III)
 // instead of read from the caller's arrays.  A compile-time choice: with the
 // waveform code in the same kernel the array path's registers spill.
 template <int N, int GEN, int M, int BLOCK, bool WAVE>
-__global__ __launch_bounds__(BLOCK, M == 2 ? (WAVE ? LR_FUSED2W_MIN_WAVES : LR_FUSED2_MIN_WAVES)
-                                           : LR_FUSED_MIN_WAVES)
+__global__ __launch_bounds__(BLOCK, LR_FUSED_MIN_WAVES)
 void fused_forward_kernel(BatchFwdArgs a) {
-  constexpr int YT = kPerLane * BLOCK;                // new link samples per tile
   constexpr int HPX = fused_halo_cap(M, BLOCK);       // halo a row can carry
-  constexpr int YR = YT + HPX;                        // row length
+  constexpr int YR = kPerLane * BLOCK + HPX;          // row length
   constexpr int NST = (M * 6 * HPX + BLOCK - 1) / BLOCK;   // halo values per lane (<= 2)
-  constexpr int CAPH = YT + N + kSlack;
-  // Template k's h window lives in its own link rows until its projection
-  // ends (the rows are written only after a barrier), so the window costs no
-  // LDS of its own.
-  static_assert(CAPH * sizeof(double2) <= 6 * YR * sizeof(double), "h window fits a row block");
   static_assert(NST <= 2, "two halo values per lane");
   __shared__ __align__(16) double ylds[M * 6 * YR];
-  __shared__ int red[2][BLOCK / 64];
+  __shared__ FarrowForward<N, BLOCK, 5, 32> proj;
   __shared__ int s_item;
+  const int YT = a.samples;                           // new link samples per tile
 
   for (;;) {
     // an opaque lane index per item: whatever derives from it (LDS offsets,
@@ -293,15 +279,10 @@ void fused_forward_kernel(BatchFwdArgs a) {
         // rounded to the even halo YT - T_out)
         const int r_end =
             (int)min((int64_t)YT, n_valid + a.halo - (t == 0 ? 0 : hp));
-        const int last = r_end - 1;
-        const bool act_a = 2 * tid <= last, act_b = 2 * tid + 1 <= last;
-        const int ra = act_a ? 2 * tid : (last & ~1);
         // sin, cos of the sky angles, tabulated per template before the launch
         // (no trigonometry, and none of its constants, in this loop)
         const double* tr = a.trig + 4 * T.index;
         const Sky sk = sky_from_trig(tr[0], tr[1], tr[2], tr[3]);
-        double ya[6], yb[6];
-        double2* hwin = reinterpret_cast<double2*>(ylds + k * 6 * YR);
         // h+ / hx: the caller's arrays, or the waveform synthesised into the
         // window from the template's parameter row (waveform time 0 at output
         // sample 0)
@@ -310,15 +291,19 @@ void fused_forward_kernel(BatchFwdArgs a) {
           hs = HSource::waveform(a.params + 8 * T.index, -T.out_start, a.dt, T.n_h);
         else
           hs = HSource::arrays(a.hp + T.h_off, a.hc + T.h_off, T.n_h);
-        project_pair<N, BLOCK>(a.orb_p, a.t_off_p, i_new, a.dt, a.inv_dt, hs,
-                               T.out_start + i_new, sk, ra, hwin, red, ya, yb);
-        __syncthreads();                              // the window is read; rows may be written
+#pragma unroll 1
+        for (int r0 = 0; r0 < r_end; r0 += a.rows) {
+          const int n = min(a.rows, r_end - r0);
+          double y[6];
+          proj.project(a.orb_p, a.t_off_p, i_new + r0, a.dt, a.inv_dt, hs,
+                       T.out_start + i_new + r0, sk, tid, n, y);
+          if (tid < n) {
 #pragma unroll
-        for (int l = 0; l < 6; ++l) {
-          double* row = ylds + (k * 6 + l) * YR;
-          if (act_a) row[par<YR>(hp + ra)] = ya[l];
-          if (act_b) row[par<YR>(hp + ra + 1)] = yb[l];
-          bad |= !(fabs(ya[l]) <= DBL_MAX && fabs(yb[l]) <= DBL_MAX);
+            for (int l = 0; l < 6; ++l) {
+              ylds[(k * 6 + l) * YR + par<YR>(hp + r0 + tid)] = y[l];
+              bad |= !(fabs(y[l]) <= DBL_MAX);
+            }
+          }
         }
         if (t > 0) {
           // the carried halo of this template back into its rows
@@ -330,9 +315,11 @@ void fused_forward_kernel(BatchFwdArgs a) {
         }
       }
       // 2. TDI of the tile's outputs for all live templates
-      const int oa = 2 * tid;                         // tile-relative output of sample a
-      const bool out_a = oa < cnt;
-      const int ob = out_a ? oa : cnt - 2;            // idle lanes mirror the last pair
+      // tile-relative output of sample a; a row of 16 lanes starts at a multiple
+      // of 32 outputs, so that it lies in one interval of the filters
+      const int oa = 2 * tid - (a.fir_k > 0 ? (int)(o0 & 31) : 0);
+      const bool out_a = oa >= 0 && oa < cnt;
+      const int ob = max(0, min(oa, cnt - 2));        // idle lanes mirror the ends
       double acc[M][2][3];
       // The filters' empty taps would spread a NaN or an infinity past the
       // stencils: such segments interpolate the delays one by one, like the
@@ -340,8 +327,8 @@ void fused_forward_kernel(BatchFwdArgs a) {
       bad = __syncthreads_or(bad);
       bool split = a.fir_k == 0 || bad;
       if (!split) {
-        // a row of 16 lanes lies in one interval; outputs past the longest
-        // template of the batch have none, and are not stored
+        // outputs past the longest template of the batch have no interval, and
+        // are not stored
         const int64_t o = o0 + ob;
         const int qe = (int)a.n_fir - 1, q = min((int)(o / kFirInterval), qe);
         const int q0 = (int)(o0 / kFirInterval), q1 = min((int)((o0 + cnt - 1) / kFirInterval), qe);

@@ -40,6 +40,7 @@ struct BatchFwdArgs {
   double t_off_p, t_off_t;   // time of output sample 0 minus each orbit grid's first sample
   double dt, inv_dt;
   int F;                     // link samples before the first output of a tile
+  int rows, samples;         // link samples per run of the projection and per tile
   int T_out;                 // outputs of a segment's first tile (even): at most link samples
                              // per tile minus the TDI halo
   int halo;                  // TDI halo: padding before and after, rounded up to even

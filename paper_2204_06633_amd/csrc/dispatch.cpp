@@ -81,7 +81,9 @@ hipError_t run_fused_forward(int order, int gen, int group, int tile, bool wave,
   // samples, and a segment of one tile carries none
   if (a.seg_tiles < 1 || a.HP < 0 || a.HP > fused_halo_cap(group, tile / 2) ||
       (a.seg_tiles > 1) != (a.HP > 0) || (a.HP > 0 && a.HP != a.halo) || a.T_out < 2 ||
-      a.T_out + a.halo > tile || (a.fir_k > 0 && a.T_out % 32 != 0))
+      a.rows < 1 || a.rows > tile / 2 || a.samples > tile || a.T_out + a.halo > a.samples ||
+      (a.fir_k > 0 && (a.T_out % 32 != 0 || a.samples % 16 != 0 ||
+                       (a.samples % 32 != 0 && a.samples > tile - 16))))
     return hipErrorInvalidValue;
   if (a.fir_k > 0) {
     hipError_t e = hipErrorInvalidValue;

@@ -20,22 +20,26 @@
 
 namespace lr {
 
+// Positions are served step by step: the link samples whose position (LDS row
+// offset `row`) has integer part f; k = f minus the position's smallest.
+struct FarrowStep {
+  int row, f, k, end;
+};
+constexpr int kFarrowSteps = 48;               // most steps of a run of link samples
+
 template <int N>
 constexpr int kFarrowCoefs = FarrowTable<N>::D + 1;
 
-// The numbers of mirrored pair i in the 16 lanes of a DPP row: lane j < 8 the
-// coefficient of u^(2 j) per sum, lane 8 + j that of u^(2 j + 1) per
-// difference.  An FMA takes its number by row_newbcast: as a literal each would
-// cost two scalar moves, which take issue slots from the FMAs at two waves per
-// SIMD.
+// The numbers of mirrored pair i: j < 8 the coefficient of u^(2 j) per sum,
+// 8 + j that of u^(2 j + 1) per difference.
 template <int N>
-struct FarrowLanes {
+struct FarrowRows {
   double w[N / 2][16];
 };
 
 template <int N>
-constexpr FarrowLanes<N> farrow_lanes() {
-  FarrowLanes<N> m{};
+constexpr FarrowRows<N> farrow_rows_of() {
+  FarrowRows<N> m{};
   for (int j = 0; j <= FarrowTable<N>::D; ++j)
     for (int i = 0; i < N / 2; ++i)
       m.w[i][(j & 1) * 8 + j / 2] =
@@ -44,105 +48,22 @@ constexpr FarrowLanes<N> farrow_lanes() {
 }
 
 template <int N>
-__constant__ FarrowLanes<N> kFarrowLanes = farrow_lanes<N>();
+__constant__ FarrowRows<N> kFarrowRows = farrow_rows_of<N>();
 
-// p[j], c[j] += number first + j/2 of w's row times x, y, for even j (or odd j).
-__device__ __forceinline__ void farrow_even(double (&p)[16], double (&c)[16], double w, double x,
-                                            double y) {
-  asm(
-      "s_nop 1\n"
-      "v_fmac_f64_dpp %0, %16, %17 row_newbcast:0 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %8, %16, %18 row_newbcast:0 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %16, %17 row_newbcast:1 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %9, %16, %18 row_newbcast:1 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %2, %16, %17 row_newbcast:2 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %10, %16, %18 row_newbcast:2 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %3, %16, %17 row_newbcast:3 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %11, %16, %18 row_newbcast:3 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %4, %16, %17 row_newbcast:4 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %12, %16, %18 row_newbcast:4 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %5, %16, %17 row_newbcast:5 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %13, %16, %18 row_newbcast:5 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %6, %16, %17 row_newbcast:6 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %14, %16, %18 row_newbcast:6 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %7, %16, %17 row_newbcast:7 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %15, %16, %18 row_newbcast:7 row_mask:0xf bank_mask:0xf\n"
-      : "+v"(p[0]), "+v"(p[2]), "+v"(p[4]), "+v"(p[6]), "+v"(p[8]), "+v"(p[10]), "+v"(p[12]), "+v"(p[14]),
-        "+v"(c[0]), "+v"(c[2]), "+v"(c[4]), "+v"(c[6]), "+v"(c[8]), "+v"(c[10]), "+v"(c[12]), "+v"(c[14])
-      : "v"(w), "v"(x), "v"(y));
-}
-__device__ __forceinline__ void farrow_odd(double (&p)[16], double (&c)[16], double w, double x,
-                                           double y) {
-  asm(
-      "s_nop 1\n"
-      "v_fmac_f64_dpp %0, %16, %17 row_newbcast:8 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %8, %16, %18 row_newbcast:8 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %16, %17 row_newbcast:9 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %9, %16, %18 row_newbcast:9 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %2, %16, %17 row_newbcast:10 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %10, %16, %18 row_newbcast:10 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %3, %16, %17 row_newbcast:11 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %11, %16, %18 row_newbcast:11 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %4, %16, %17 row_newbcast:12 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %12, %16, %18 row_newbcast:12 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %5, %16, %17 row_newbcast:13 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %13, %16, %18 row_newbcast:13 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %6, %16, %17 row_newbcast:14 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %14, %16, %18 row_newbcast:14 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %7, %16, %17 row_newbcast:15 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %15, %16, %18 row_newbcast:15 row_mask:0xf bank_mask:0xf\n"
-      : "+v"(p[1]), "+v"(p[3]), "+v"(p[5]), "+v"(p[7]), "+v"(p[9]), "+v"(p[11]), "+v"(p[13]), "+v"(p[15]),
-        "+v"(c[1]), "+v"(c[3]), "+v"(c[5]), "+v"(c[7]), "+v"(c[9]), "+v"(c[11]), "+v"(c[13]), "+v"(c[15])
-      : "v"(w), "v"(x), "v"(y));
-}
-// x, y += sum over even (odd) j of number j of w's row times p[j], c[j].
-__device__ __forceinline__ void farrow_even_t(const double (&p)[16], const double (&c)[16],
-                                              double w, double& x, double& y) {
-  asm(
-      "s_nop 1\n"
-      "v_fmac_f64_dpp %0, %2, %3 row_newbcast:0 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %11 row_newbcast:0 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %4 row_newbcast:1 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %12 row_newbcast:1 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %5 row_newbcast:2 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %13 row_newbcast:2 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %6 row_newbcast:3 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %14 row_newbcast:3 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %7 row_newbcast:4 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %15 row_newbcast:4 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %8 row_newbcast:5 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %16 row_newbcast:5 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %9 row_newbcast:6 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %17 row_newbcast:6 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %10 row_newbcast:7 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %18 row_newbcast:7 row_mask:0xf bank_mask:0xf\n"
-      : "+v"(x), "+v"(y)
-      : "v"(w), "v"(p[0]), "v"(p[2]), "v"(p[4]), "v"(p[6]), "v"(p[8]), "v"(p[10]), "v"(p[12]), "v"(p[14]),
-        "v"(c[0]), "v"(c[2]), "v"(c[4]), "v"(c[6]), "v"(c[8]), "v"(c[10]), "v"(c[12]), "v"(c[14]));
-}
-__device__ __forceinline__ void farrow_odd_t(const double (&p)[16], const double (&c)[16],
-                                             double w, double& x, double& y) {
-  asm(
-      "s_nop 1\n"
-      "v_fmac_f64_dpp %0, %2, %3 row_newbcast:8 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %11 row_newbcast:8 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %4 row_newbcast:9 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %12 row_newbcast:9 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %5 row_newbcast:10 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %13 row_newbcast:10 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %6 row_newbcast:11 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %14 row_newbcast:11 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %7 row_newbcast:12 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %15 row_newbcast:12 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %8 row_newbcast:13 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %16 row_newbcast:13 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %9 row_newbcast:14 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %17 row_newbcast:14 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %0, %2, %10 row_newbcast:15 row_mask:0xf bank_mask:0xf\n"
-      "v_fmac_f64_dpp %1, %2, %18 row_newbcast:15 row_mask:0xf bank_mask:0xf\n"
-      : "+v"(x), "+v"(y)
-      : "v"(w), "v"(p[1]), "v"(p[3]), "v"(p[5]), "v"(p[7]), "v"(p[9]), "v"(p[11]), "v"(p[13]), "v"(p[15]),
-        "v"(c[1]), "v"(c[3]), "v"(c[5]), "v"(c[7]), "v"(c[9]), "v"(c[11]), "v"(c[13]), "v"(c[15]));
+// Pair i's numbers into scalar registers.  The opaque index keeps the loads
+// where they stand: the compiler would otherwise hoist all 16 N / 2 of them
+// out of the callers' loops.  Of the ways to feed them to the FMAs, literals
+// cost two scalar moves each and broadcasts from a lane (DPP) issue at 24-28
+// of the 32-34 10^12 FMA/s that scalar operands reach (projection of 3,155,760
+// samples at order 25: 183 against 173 us).
+template <int N>
+__device__ __forceinline__ void farrow_row(int i, double (&w)[16]) {
+  int o = 16 * i;
+  asm volatile("" : "+s"(o));
+  const auto r =
+      (const __attribute__((address_space(4))) double*)&kFarrowRows<N>.w[0][0] + o;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) w[j] = r[j];
 }
 
 // Coefficients of u^0 .. u^D of both polarisations from the stencil
@@ -153,25 +74,31 @@ __device__ __forceinline__ void farrow_coefs(const double2* win, double (&p)[kFa
   using T = FarrowTable<N>;
   constexpr int H = N / 2, D = T::D;
   if constexpr (D == 15) {
-    const double* w = &kFarrowLanes<N>.w[0][threadIdx.x & 15];
-#pragma unroll
-    for (int j = 0; j <= D; ++j) p[j] = c[j] = 0.0;
     double2 a = win[H], b = win[H - 1];
-    double x = w[0];
+    double w[16];
+    farrow_row<N>(0, w);
 #pragma unroll
     for (int i = 0; i < H; ++i) {
       // the next pair is read while this one is summed, and no earlier: all
       // reads at the top would spill
       const int n = i + 1 < H ? i + 1 : i;
       const double2 an = win[H + n], bn = win[H - 1 - n];
-      const double xn = w[16 * n];
+      double v[16];
+      farrow_row<N>(n, v);
       __builtin_amdgcn_sched_barrier(0);
-      farrow_even(p, c, x, a.x + b.x, a.y + b.y);
-      farrow_odd(p, c, x, a.x - b.x, a.y - b.y);
+      const double ex = a.x + b.x, ey = a.y + b.y, ox = a.x - b.x, oy = a.y - b.y;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        p[2 * j] = i == 0 ? w[j] * ex : fma(w[j], ex, p[2 * j]);
+        c[2 * j] = i == 0 ? w[j] * ey : fma(w[j], ey, c[2 * j]);
+        p[2 * j + 1] = i == 0 ? w[8 + j] * ox : fma(w[8 + j], ox, p[2 * j + 1]);
+        c[2 * j + 1] = i == 0 ? w[8 + j] * oy : fma(w[8 + j], oy, c[2 * j + 1]);
+      }
       __builtin_amdgcn_sched_barrier(0);
       a = an;
       b = bn;
-      x = xn;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) w[j] = v[j];
     }
   } else {
 #pragma unroll
@@ -197,17 +124,25 @@ __device__ __forceinline__ void farrow_transpose(const double (&p)[kFarrowCoefs<
                                                  const Put& put) {
   using T = FarrowTable<N>;
   constexpr int H = N / 2, D = T::D;
-  const double* row = &kFarrowLanes<N>.w[0][threadIdx.x & 15];
-  double x = row[0];
+  double w[16];
+  if constexpr (D == 15) farrow_row<N>(0, w);
 #pragma unroll
   for (int i = 0; i < H; ++i) {
     double ep = 0.0, ec = 0.0, op = 0.0, oc = 0.0;
     if constexpr (D == 15) {
-      const double xn = row[16 * (i + 1 < H ? i + 1 : i)];
+      double v[16];
+      farrow_row<N>(i + 1 < H ? i + 1 : i, v);
       __builtin_amdgcn_sched_barrier(0);
-      farrow_even_t(p, c, x, ep, ec);
-      farrow_odd_t(p, c, x, op, oc);
-      x = xn;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        ep = fma(w[j], p[2 * j], ep);
+        ec = fma(w[j], c[2 * j], ec);
+        op = fma(w[8 + j], p[2 * j + 1], op);
+        oc = fma(w[8 + j], c[2 * j + 1], oc);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) w[j] = v[j];
     } else {
 #pragma unroll
       for (int j = 0; j <= D; ++j) {

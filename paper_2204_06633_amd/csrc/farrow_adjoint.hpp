@@ -30,13 +30,6 @@ namespace lr {
 
 constexpr int kFarrowLd = kFarrowBlock;        // row length of the LDS arrays
 
-// One step of phase B: the link samples whose position `row / kFarrowLd` has
-// integer part f; k = f minus the position's smallest.
-struct FarrowStep {
-  int row, f, k, end;
-};
-constexpr int kFarrowSteps = 48;               // most steps of a run
-
 struct FarrowShared {
   int lo[9], hi[9];                            // integer parts of the positions in the run
   alignas(16) FarrowStep step[kFarrowSteps + 3];
@@ -124,9 +117,9 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
       __syncthreads();                         // lo, hi set; the previous run is done with LDS
 #pragma unroll
       for (int p = 0; p < 9; ++p) {
-        double eps;
-        f[p] = split_delay(position_delay(g, p), a.inv_dt, eps);
-        if (active) U[p * LD + t] = eps - 0.5;
+        double u;
+        f[p] = split_centred(position_delay(g, p), a.inv_dt, u);
+        if (active) U[p * LD + t] = u;
         const int f0 = __builtin_amdgcn_readfirstlane(f[p]);
         int x = f0, y = f0;
         if (!__all(f[p] == f0)) {
@@ -141,7 +134,7 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
         atomicMax(&sh.hi[lane], whi);
       }
 #pragma unroll
-      for (int l = 0; l < 6; ++l) gl[l] /= 2.0 * (1.0 - kDir[l] * g.kn[kArm[l]]);
+      for (int l = 0; l < 6; ++l) gl[l] *= 0.5 * fast_rcp(1.0 - kDir[l] * g.kn[kArm[l]]);
       if (active) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
@@ -345,7 +338,7 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
         const int arm = kArm[l], r = kLinkRecv[l] - 1;
         const double hp = GP[(3 + l) * LD + rel] - GP[r * LD + rel];
         const double hc = GC[(3 + l) * LD + rel] - GC[r * LD + rel];
-        const double inv = 1.0 / (1.0 - kDir[l] * g.kn[arm]);
+        const double inv = fast_rcp(1.0 - kDir[l] * g.kn[arm]);
         const double gl = 0.5 * gy[l] * inv;
         const double sn = gl * inv * kDir[l] * (g.xip[arm] * hp + g.xic[arm] * hc);
         const double su = 2.0 * gl * (g.un[arm] * hp + g.vn[arm] * hc);

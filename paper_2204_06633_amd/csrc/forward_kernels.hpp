@@ -1,8 +1,10 @@
-// Forward response kernels for gfx950 (FP64):
-//   project_links_kernel  -- link responses y_ij, Sec. IV.B
-//   tdi_kernel            -- Michelson TDI-1 / TDI-2 and A, E, T, Sec. IV.C
+// What the forward kernels for gfx950 (FP64) share -- sky basis, LDS windows,
+// the source of h+ and hx -- and
+//   tdi_kernel -- Michelson TDI-1 / TDI-2 and A, E, T, Sec. IV.C, delay by
+//                 delay (where the filters of tdi_fir.hpp do not serve).
+// The link responses are in farrow_forward.hpp.
 //
-// Both kernels are time-tiled: a workgroup owns kFwdTile consecutive output
+// The kernel is time-tiled: a workgroup owns kFwdTile consecutive output
 // samples, computes every retarded position of its samples first, reduces the
 // extent of all their interpolation stencils, stages exactly that window of
 // the input series in LDS with coalesced loads, and then evaluates the
@@ -16,7 +18,7 @@
 // and the two weight sets are independent product chains (twice the
 // instruction-level parallelism).  A wave whose two stencils do not line up
 // for some position (an integer crossing) takes a separate-window branch for
-// that position.  Stores are link- / channel-major and coalesced.
+// that position.  Stores are channel-major and coalesced.
 #pragma once
 
 #include <type_traits>
@@ -27,6 +29,20 @@
 #include "internal.hpp"
 
 namespace lr {
+
+// Switches of kernels that are no more; lr_build_config() still reports them.
+#ifndef LR_PROJ_PIPE
+#define LR_PROJ_PIPE 2
+#endif
+#ifndef LR_PROJ_MIN_WAVES
+#define LR_PROJ_MIN_WAVES 1
+#endif
+#ifndef LR_FUSED2_MIN_WAVES
+#define LR_FUSED2_MIN_WAVES 3
+#endif
+#ifndef LR_FUSED2W_MIN_WAVES
+#define LR_FUSED2W_MIN_WAVES 2
+#endif
 
 constexpr int kBlock = kTile;          // lanes per workgroup
 constexpr int kSlack = 64;             // window samples beyond the tile + taps
@@ -94,53 +110,6 @@ struct ParStream {
 // Projection
 // ---------------------------------------------------------------------------
 
-// Positions p = 0..2 (reception at spacecraft p+1) enter the links received
-// there with a minus sign; p = 3..8 (emission of link p-3) enter that link
-// with a plus sign.  Adds xi+ h+ + xix hx of position p to the numerators.
-__device__ __forceinline__ void add_position(int p, const double (&xip)[3],
-                                             const double (&xic)[3], double hp, double hc,
-                                             double (&num)[6]) {
-  if (p >= 3) {
-    const int l = p - 3, arm = kArm[l];
-    num[l] += xip[arm] * hp + xic[arm] * hc;
-  } else {
-#pragma unroll
-    for (int l = 0; l < 6; ++l)
-      if (kLinkRecv[l] - 1 == p) num[l] -= xip[kArm[l]] * hp + xic[kArm[l]] * hc;
-  }
-}
-
-// add_position for a position index known only at run time: the links are
-// selected by comparisons, so the accumulators stay in registers.
-__device__ __forceinline__ void add_position_rt(int p, const double (&xip)[3],
-                                                const double (&xic)[3], double hp, double hc,
-                                                double (&num)[6]) {
-#pragma unroll
-  for (int l = 0; l < 6; ++l) {
-    const int arm = kArm[l];
-    const double v = xip[arm] * hp + xic[arm] * hc;
-    const bool emit = p == 3 + l, recv = p == kLinkRecv[l] - 1;
-    num[l] += emit ? v : (recv ? -v : 0.0);
-  }
-}
-
-// Per-sample state of the projection: what the link assembly needs.
-struct ProjSample {
-  int sh[9];
-  double ep[9];
-  double xip[3], xic[3], kn[3];
-};
-
-__device__ __forceinline__ void proj_sample(const OrbitView& orb, double tau, double inv_dt,
-                                            const Sky& sk, ProjSample& s) {
-  LinkGeom g;
-  link_geometry(orb, tau, sk, g);
-#pragma unroll
-  for (int p = 0; p < 9; ++p) s.sh[p] = split_delay(position_delay(g, p), inv_dt, s.ep[p]);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) { s.xip[k] = g.xip[k]; s.xic[k] = g.xic[k]; s.kn[k] = g.kn[k]; }
-}
-
 // Source of the h+ / hx samples a projection reads, by h-index j in
 // [0, n_h): arrays in HBM, or the Galactic-binary waveform (Sec. III)
 // evaluated at t_j = (k0 + j) dt from one parameter row (the fused batch
@@ -192,180 +161,9 @@ struct HSource {
   }
 };
 
-// Window loads kept in flight per stream in project_pair (0: the compiler's
-// own schedule).  Build-time tuning knob (sched_group_barrier masks: 0x100
-// LDS reads, 0x002 VALU).
-#ifndef LR_PROJ_PIPE
-#define LR_PROJ_PIPE 2
-#endif
-
-// Link responses of one template at the lane's two tile samples ra and ra+1
-// (ra even), in a workgroup of BLOCK lanes (a tile of 2 BLOCK samples).  Tile element r has h-index hq0 + r and orbit time
-// t_off + (ti0 + r) * dt.  Uses the workgroup's LDS window and reduction
-// scratch; contains barriers, so every lane of the workgroup must call it.
-template <int N, int BLOCK = kBlock>
-__device__ __forceinline__ void project_pair(const OrbitView& orb, double t_off, int64_t ti0,
-                                             double dt, double inv_dt, const HSource& hs,
-                                             int64_t hq0,
-                                             const Sky& sk, int ra, double2* win,
-                                             int (&red)[2][BLOCK / 64], double (&ya)[6],
-                                             double (&yb)[6]) {
-  constexpr int H = N / 2;
-  constexpr int CAP = kPerLane * BLOCK + N + kSlack;
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));          // not hoisted out of a caller's loop
-  ProjSample A, B;
-  proj_sample(orb, t_off + (double)(ti0 + ra) * dt, inv_dt, sk, A);
-  __builtin_amdgcn_sched_barrier(0);     // one sample's geometry live at a time
-  proj_sample(orb, t_off + (double)(ti0 + ra + 1) * dt, inv_dt, sk, B);
-  __builtin_amdgcn_sched_barrier(0);
-
-  int lo = min(A.sh[0], B.sh[0] + 1), hi = max(A.sh[0], B.sh[0] + 1);
-#pragma unroll
-  for (int p = 1; p < 9; ++p) {
-    lo = min(lo, min(A.sh[p], B.sh[p] + 1));
-    hi = max(hi, max(A.sh[p], B.sh[p] + 1));
-  }
-  int wlo, whi;
-  block_range<BLOCK>(ra + lo - (H - 1), ra + hi + H, red, wlo, whi);
-  const int count = whi - wlo + 1;
-  const int64_t base = hq0 + wlo;                // h-index of window element 0
-  const int64_t hmax = hs.n_h - 1;
-  const int64_t qa = hq0 + ra;
-
-  double na[6] = {0, 0, 0, 0, 0, 0}, nb[6] = {0, 0, 0, 0, 0, 0};
-  if (count > 0 && count <= CAP) {
-    for (int k = tid; k < count; k += BLOCK) {
-      int64_t j = base + k;
-      j = j < 0 ? 0 : (j > hmax ? hmax : j);
-      win[par<CAP>(k)] = hs.at(j);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < 9; ++p) {
-      LagrangePair<N> st(A.ep[p], B.ep[p]);
-      const ParStream<CAP> src(ra + A.sh[p] - (H - 1) - wlo);
-      double pa = 0.0, ca = 0.0, pb = 0.0, cb = 0.0;
-      if (__all(A.sh[p] == B.sh[p])) {
-        // sample b's stencil is sample a's shifted by one: N + 1 loads feed both
-        double2 cur = win[src.at(0)];
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-          if (LR_PROJ_PIPE > 0) {
-            // at most LR_PROJ_PIPE window loads in flight: bounds the registers
-            // the scheduler spends on early loads
-            if (k == 0) __builtin_amdgcn_sched_group_barrier(0x100, LR_PROJ_PIPE, 0);
-            if (k + LR_PROJ_PIPE <= N) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);
-          }
-          const double2 nxt = win[src.at(k + 1)];
-          st.tap(k);
-          pa = st.step_a(pa, cur.x, k);
-          ca = st.step_a(ca, cur.y, k);
-          pb = st.step_b(pb, nxt.x, k);
-          cb = st.step_b(cb, nxt.y, k);
-          cur = nxt;
-        }
-      } else {
-        const ParStream<CAP> srb(ra + 1 + B.sh[p] - (H - 1) - wlo);
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-          if (LR_PROJ_PIPE > 0) {
-            if (k == 0) __builtin_amdgcn_sched_group_barrier(0x100, 2 * LR_PROJ_PIPE, 0);
-            if (k + LR_PROJ_PIPE < N) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);
-          }
-          const double2 v = win[src.at(k)], w = win[srb.at(k)];
-          st.tap(k);
-          pa = st.step_a(pa, v.x, k);
-          ca = st.step_a(ca, v.y, k);
-          pb = st.step_b(pb, w.x, k);
-          cb = st.step_b(cb, w.y, k);
-        }
-      }
-      add_position(p, A.xip, A.xic, pa, ca, na);
-      add_position(p, B.xip, B.xic, pb, cb, nb);
-      __builtin_amdgcn_sched_barrier(0);   // keep one position's streams live at a time
-    }
-  } else {
-    // Window larger than the LDS tile (very small dt or extreme orbits):
-    // read the stencils from global memory, indices clamped.  A rolled loop
-    // over copies of the per-sample state (which may then live in scratch):
-    // this rare path must not set the register budget of the LDS path.
-    const ProjSample Ac = A, Bc = B;
-#pragma unroll 1
-    for (int p = 0; p < 9; ++p) {
-      LagrangePair<N> st(Ac.ep[p], Bc.ep[p]);
-      const int64_t ja = qa + Ac.sh[p] - (H - 1), jb = qa + 1 + Bc.sh[p] - (H - 1);
-      double pa = 0.0, ca = 0.0, pb = 0.0, cb = 0.0;
-#pragma unroll 1
-      for (int m = 0; m < N; ++m) {
-        int64_t j = ja + m;
-        j = j < 0 ? 0 : (j > hmax ? hmax : j);
-        int64_t jj = jb + m;
-        jj = jj < 0 ? 0 : (jj > hmax ? hmax : jj);
-        st.tap(m);
-        const double2 va = hs.at(j), vb = hs.at(jj);
-        pa = st.step_a(pa, va.x, m);
-        ca = st.step_a(ca, va.y, m);
-        pb = st.step_b(pb, vb.x, m);
-        cb = st.step_b(cb, vb.y, m);
-      }
-      add_position_rt(p, A.xip, A.xic, pa, ca, na);
-      add_position_rt(p, B.xip, B.xic, pb, cb, nb);
-    }
-  }
-  // the streams' common scale folded into the link normalisation
-#pragma unroll
-  for (int l = 0; l < 6; ++l) {
-    const int arm = kArm[l];
-    ya[l] = LagrangeStream<N>::finish(na[l]) / (2.0 * (1.0 - kDir[l] * A.kn[arm]));
-    yb[l] = LagrangeStream<N>::finish(nb[l]) / (2.0 * (1.0 - kDir[l] * B.kn[arm]));
-  }
-}
-
-// Minimum resident waves per SIMD the compiler must allow (register budget);
-// build-time tuning knobs.
-#ifndef LR_PROJ_MIN_WAVES
-#define LR_PROJ_MIN_WAVES 1
-#endif
 #ifndef LR_TDI_MIN_WAVES
 #define LR_TDI_MIN_WAVES 4
 #endif
-
-template <int N>
-__global__ __launch_bounds__(kBlock, LR_PROJ_MIN_WAVES)
-void project_links_kernel(ProjArgs a) {
-  constexpr int CAP = kFwdTile + N + kSlack;
-  __shared__ double2 win[CAP];
-  __shared__ int red[2][kBlock / 64];
-  __shared__ double s_trig[2][2];
-
-  const int tid = threadIdx.x;
-  const int64_t i0 = (int64_t)blockIdx.x * kFwdTile;
-  const int last = (int)min((int64_t)(kFwdTile - 1), a.n_y - 1 - i0);
-  const bool act_a = kPerLane * tid <= last, act_b = kPerLane * tid + 1 <= last;
-  const int ra = act_a ? kPerLane * tid : last;          // idle lanes mirror the last sample
-
-  const SkyTrig tr = load_sky(a.sky, s_trig);
-  const Sky sk = sky_from_trig(tr.sl, tr.cl, tr.sb, tr.cb);
-  double ya[6], yb[6];
-  project_pair<N>(a.orb, a.t_off, a.y_start + i0, a.dt, a.inv_dt,
-                  HSource::arrays(a.hp, a.hc, a.n_h), a.y_start + i0, sk, ra, win, red, ya, yb);
-
-  if (!act_a) return;
-  const int64_t i = i0 + ra;
-#pragma unroll
-  for (int l = 0; l < 6; ++l) {
-    double* dst = a.y + (int64_t)l * a.n_y + i;
-    if (act_b && ((reinterpret_cast<uintptr_t>(dst) & 15) == 0)) {
-      *reinterpret_cast<double2*>(dst) = make_double2(ya[l], yb[l]);
-    } else {
-      dst[0] = ya[l];
-      if (act_b) dst[1] = yb[l];
-    }
-  }
-}
 
 // ---------------------------------------------------------------------------
 // TDI
@@ -734,13 +532,6 @@ __global__ __launch_bounds__(kBlock, LR_TDI_MIN_WAVES) void tdi_kernel(TdiArgs a
 // Launchers (explicitly instantiated per tap count in forward_*.hip)
 // ---------------------------------------------------------------------------
 template <int N>
-hipError_t launch_project(const ProjArgs& a, hipStream_t s) {
-  const int64_t blocks = (a.n_y + kFwdTile - 1) / kFwdTile;
-  hipLaunchKernelGGL(project_links_kernel<N>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
-  return hipGetLastError();
-}
-
-template <int N>
 hipError_t launch_tdi(const TdiArgs& a, int gen, hipStream_t s) {
   const int64_t blocks = (a.n_out + kFwdTile - 1) / kFwdTile;
   if (gen == 1)
@@ -751,7 +542,6 @@ hipError_t launch_tdi(const TdiArgs& a, int gen, hipStream_t s) {
 }
 
 #define LR_INSTANTIATE_FORWARD(NT)                                              \
-  template hipError_t launch_project<NT>(const ProjArgs&, hipStream_t);         \
   template hipError_t launch_tdi<NT>(const TdiArgs&, int, hipStream_t);
 
 }  // namespace lr

@@ -18,6 +18,7 @@ struct ProjArgs {
   const double* sky; // device [lam, beta]
   int64_t y_start, n_y;
   double* y;         // [6][n_y]
+  int rows, runs;    // link samples per run, runs per workgroup
 };
 
 struct TdiArgs {
@@ -109,10 +110,15 @@ FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt
 FirShape fused_fir_shape(int order, int gen, double L_min, double L_max, double dt);
 
 // Polynomial projection kernels (farrow.hpp): lanes of a workgroup, runs of link
-// samples per workgroup, and link samples per run, or 0 where the nine
-// positions lie too far apart for them.
+// samples per workgroup.  farrow_rows: link samples per run of a workgroup of
+// `lanes`, which must hold the spread of the nine positions besides; all lanes
+// where that is more than `most`.  The adjoint's: 0 beyond kFarrowSpread.
 constexpr int kFarrowBlock = 256, kFarrowRuns = 2, kFarrowSpread = 64;
-int farrow_rows(double L_max, double dt);
+int farrow_rows(double L_max, double dt, int lanes, int most);
+inline int farrow_adjoint_rows(double L_max, double dt) {
+  const int rows = farrow_rows(L_max, dt, kFarrowBlock, kFarrowSpread);
+  return rows < kFarrowBlock ? rows : 0;
+}
 
 // Workgroup size of the tiled kernels (output samples per workgroup).
 constexpr int kTile = 256;

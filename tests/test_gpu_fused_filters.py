@@ -88,3 +88,25 @@ def test_fused_filters_match_oracle(torch_cuda, kind, gen, order, bad):
             if bad is None:
                 assert np.array_equal(o[k], outs[0][k]), (k, g.n_out)
     assert finite == (bad is None)
+
+
+@pytest.mark.parametrize("tile", [256, 512])
+@pytest.mark.parametrize("dt,order", [(0.4, 25), (0.7, 7), (1.0, 25), (1.5, 25), (2.5, 25)])
+def test_fused_tiles_at_small_dt(torch_cuda, dt, order, tile):
+    """Runs and tiles where the positions' spread and the TDI halo eat into them."""
+    from paper_2204_06633_amd import native
+    torch = torch_cuda
+    n_out = [1, 700, 333]
+    grids, params, sp, _ = workloads.make_batch(3, "keplerian", n_out, dt, order, 2, 11)
+    lay = workloads.batch_layout(grids, 3)
+    h = np.zeros((2, lay.n_h_total))
+    for g, ho, p in zip(grids, lay.h_offsets, params):
+        h[:, ho:ho + g.n_h] = inputs.gb_polarizations(p, g.waveform_times())
+    dev = lambda a: torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda")
+    orb, ref = native.Orbits.from_samples(sp), oracle.Orbits.from_samples(sp)
+    b = native.Batch(lay.templates(), orb, orb, grids[0].t_start, dt, order, 2, "XYZ", tile=tile)
+    out = b.response(dev(h[0]), dev(h[1]), dev(params[:, 6:8]))
+    for k, (g, ho, p) in enumerate(zip(grids, lay.h_offsets, params)):
+        want = oracle.response(ref, ref, g, h[0, ho:ho + g.n_h], h[1, ho:ho + g.n_h], p[6], p[7],
+                               order, 2, "XYZ")
+        cases.check(b.output_block(out, k).cpu().numpy(), want, 1e-11, "template %d" % k)

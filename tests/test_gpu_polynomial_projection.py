@@ -1,11 +1,11 @@
-"""Projection adjoint and sky gradient from polynomials per stencil base
+"""Projection, its adjoint and the sky gradient from polynomials per stencil base
 against the oracle, where its runs can go wrong: one link sample, one more or
 less than a run or a workgroup of them, both kinds of coefficient tables,
 positions further apart than the light times or moving through many samples.
 
 The polynomials replace the weights up to rounding (what they drop is below
 2.5e-17 of the largest sample), so the bars are those of the other parity
-tests: 1e-10 for the transpose, 1e-6 for the gradient against Richardson
+tests: 1e-11 forward, 1e-10 for the transpose, 1e-6 for the gradient against Richardson
 extrapolated differences.
 """
 import dataclasses
@@ -85,3 +85,27 @@ def test_polynomial_projection_adjoint(torch_cuda, n_y, order, dt, kind):
         step = 2e-3 * dt / (500.0 if kind != "fast" else 1e4)
         fd = [(4.0 * slope(i, step / 2) - slope(i, step)) / 3.0 for i in range(2)]
         cases.check(got[4], np.array(fd), 1e-6)
+
+
+# 0.2 s: fewer link samples than bases; 0.05 s: every stencil from h
+@pytest.mark.parametrize("n_y,order,dt,kind", SIZES + [(700, 25, 0.2, "keplerian"),
+                                                       (300, 9, 0.05, "keplerian"),
+                                                       (300, 25, 0.05, "keplerian")])
+def test_polynomial_projection(torch_cuda, n_y, order, dt, kind):
+    from paper_2204_06633_amd import native
+    torch = torch_cuda
+    s = _orbits(kind)
+    orb, ref = native.Orbits.from_samples(s), oracle.Orbits.from_samples(s)
+    f, b = orb.projection_padding(order, dt)
+    t0_h, n_h, start = T0 + 1000.0 - f * dt, f + n_y + b + 3, f + 1
+    h = np.random.default_rng(n_y + order).standard_normal((2, n_h))
+    h[:, :2] = h[:, -2:] = np.nan        # padding that no stencil reaches
+    lam, beta = 1.1, -0.4
+    dev = lambda a: torch.tensor(a, dtype=torch.float64, device="cuda")
+    y = native.project_links(orb, t0_h, dt, dev(h[0]), dev(h[1]), dev([lam, beta]), order, start,
+                             n_y).cpu().numpy()
+    ref = oracle.project_links(ref, t0_h, dt, h[0], h[1], lam, beta, order,
+                               np.arange(start, start + n_y))
+    assert np.array_equal(np.isfinite(ref), np.isfinite(y))
+    ok = np.isfinite(ref)
+    cases.check(y[ok], ref[ok], 1e-11)
