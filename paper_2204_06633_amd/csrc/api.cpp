@@ -548,11 +548,9 @@ int lr_project_adjoint(const lr_orbits* orb, double t0_h, double dt, int64_t n_h
   a.params = nullptr;
   a.k0 = 0;
   a.gb_part = nullptr;
-  // Without the sky gradient the carry kernel is the faster one at low orders
-  // (3,155,760 samples at dt = 10 s: order 7 236 against 247 us, order 13 277
-  // against 276, order 25 385 against 313); with it the polynomials always are
-  // (order 1 368 against 324, order 25 804 against 570).
-  a.rows = g_sky || order >= 15 ? lr::farrow_adjoint_rows(orb->L_max, dt) : 0;
+  // 0 where the positions' spread leaves too few link samples (dt below 0.27 s):
+  // the kernels that scatter by weights
+  a.rows = lr::farrow_adjoint_rows(orb->L_max, dt);
   e = lr::run_project_adjoint(order, a, s);
   const int64_t tile = a.rows > 0 ? lr::kFarrowRuns * a.rows : lr::kTile;      // link samples per partial sum
   if (e == hipSuccess && g_sky)

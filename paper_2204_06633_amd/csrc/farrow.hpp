@@ -20,13 +20,6 @@
 
 namespace lr {
 
-// Positions are served step by step: the link samples whose position (LDS row
-// offset `row`) has integer part f; k = f minus the position's smallest.
-struct FarrowStep {
-  int row, f, k, end;
-};
-constexpr int kFarrowSteps = 48;               // most steps of a run of link samples
-
 template <int N>
 constexpr int kFarrowCoefs = FarrowTable<N>::D + 1;
 

@@ -19,8 +19,10 @@
 //
 // Bound by FP64 issue at two waves per SIMD (registers: 64 coefficients and
 // coefficient gradients per lane).  One year at dt = 10 s, order 25, against
-// nine weight sequences per link sample: with the sky gradient 804 -> 570 us,
-// without 385 -> 313 us.
+// nine weight sequences per link sample: with the sky gradient 804 -> 506 us,
+// without 380 -> 245 us (order 1: 191 -> 150; order 13: 272 -> 209).  With
+// predicates and a list of steps in phase B throughout, as where integer parts
+// cross within a run, 541 and 306 us.
 #pragma once
 
 #include "batch_adjoint_kernels.hpp"
@@ -28,15 +30,25 @@
 
 namespace lr {
 
-constexpr int kFarrowLd = kFarrowBlock;        // row length of the LDS arrays
+// Rows of the LDS arrays: the quick path of phase B takes positions up to
+// kFarrowPad apart, where a base's link sample is its lane minus up to that; what
+// lies before a row's first link sample is zero.
+constexpr int kFarrowPad = 16, kFarrowLd = kFarrowBlock + kFarrowPad;
+
+// A step of phase B's general path: the link samples whose position `row` has
+// integer part f; k = f minus the position's smallest.
+struct FarrowStep {
+  int row, f, k, end;
+};
+constexpr int kFarrowSteps = 48;               // most steps of a run
 
 struct FarrowShared {
-  int lo[9], hi[9];                            // integer parts of the positions in the run
+  int lo[kFarrowBlock / 64][9], hi[kFarrowBlock / 64][9];   // per wave: integer parts
   alignas(16) FarrowStep step[kFarrowSteps + 3];
   double s_trig[2][2];
   double s_part[9][kFarrowBlock / 64];         // per wave: sky gradient, waveform sums
   gb::Source src;
-  unsigned char f[9 * kFarrowLd];              // integer part minus lo
+  unsigned char f[9 * kFarrowBlock];           // integer part minus lo
 };
 
 // Doubles of dynamic LDS: u and the two gradients per position and link
@@ -51,9 +63,9 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
                                                     double* part_out) {
   constexpr int H = N / 2, D = FarrowTable<N>::D, LD = kFarrowLd, WR = 64 + N;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  double* U = lds;
-  double* GP = lds + 9 * LD;
-  double* GC = lds + 18 * LD;
+  double* U = lds + kFarrowPad;
+  double* GP = U + 9 * LD;
+  double* GC = U + 18 * LD;
   double2* win = reinterpret_cast<double2*>(lds + 27 * LD);
   double* sums = lds + 27 * LD + (SKY ? 2 * (kFarrowBlock + N) : 0);
   double* mine = sums + wv * 2 * WR;
@@ -69,6 +81,8 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
   // h+ and hx: the arrays, or the waveform with its constants kept in LDS
   if (WAVE && tid == 0) sh.src = gb::load_source(a.params);
   if (lane < 9) sh.s_part[lane][wv] = 0.0;
+  for (int e = tid; e < 27 * kFarrowPad; e += kFarrowBlock)
+    U[e / kFarrowPad * LD - 1 - e % kFarrowPad] = 0.0;
   __syncthreads();
   auto source = [&]() {
     if constexpr (WAVE) {
@@ -98,11 +112,7 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
     const double tau = a.t_off + (double)(q0 + rel) * a.dt;
 
     // A.
-    if (t < 9) {
-      sh.lo[t] = 1 << 30;
-      sh.hi[t] = -(1 << 30);
-    }
-    int lo[9], hi[9];
+    int f[9], wlo = 0;                         // lane p < 9: the range of position p
     {
       double gl[6];
 #pragma unroll
@@ -113,86 +123,100 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
       LinkGeom g;
       const SkyTrig tr = trig();
       link_geometry(a.orb, tau, sky_from_trig(tr.sl, tr.cl, tr.sb, tr.cb), g);
-      int f[9], wlo = 0, whi = 0;              // lane p < 9: the wave's range of position p
-      __syncthreads();                         // lo, hi set; the previous run is done with LDS
+      double u[9];
+      int differ = 0;
 #pragma unroll
       for (int p = 0; p < 9; ++p) {
-        double u;
-        f[p] = split_centred(position_delay(g, p), a.inv_dt, u);
-        if (active) U[p * LD + t] = u;
+        f[p] = split_centred(position_delay(g, p), a.inv_dt, u[p]);
         const int f0 = __builtin_amdgcn_readfirstlane(f[p]);
-        int x = f0, y = f0;
-        if (!__all(f[p] == f0)) {
-          x = wave_min(f[p]);
-          y = wave_max(f[p]);
+        differ |= f[p] ^ f0;
+        wlo = lane == p ? f0 : wlo;
+      }
+      int whi = wlo;
+      if (__any(differ)) {
+#pragma unroll
+        for (int p = 0; p < 9; ++p) {
+          const int x = wave_min(f[p]), y = wave_max(f[p]);
+          wlo = lane == p ? x : wlo;
+          whi = lane == p ? y : whi;
         }
-        wlo = lane == p ? x : wlo;
-        whi = lane == p ? y : whi;
       }
       if (lane < 9) {
-        atomicMin(&sh.lo[lane], wlo);
-        atomicMax(&sh.hi[lane], whi);
+        sh.lo[wv][lane] = wlo;
+        sh.hi[wv][lane] = whi;
       }
 #pragma unroll
       for (int l = 0; l < 6; ++l) gl[l] *= 0.5 * fast_rcp(1.0 - kDir[l] * g.kn[kArm[l]]);
-      if (active) {
+      __syncthreads();                         // lo, hi; the previous run is done with LDS
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          double vp = 0.0, vc = 0.0;
+      for (int i = 0; i < 3; ++i) {
+        double vp = 0.0, vc = 0.0;
 #pragma unroll
-          for (int l = 0; l < 6; ++l)
-            if (kLinkRecv[l] - 1 == i) {
-              vp = fma(-gl[l], g.xip[kArm[l]], vp);
-              vc = fma(-gl[l], g.xic[kArm[l]], vc);
-            }
-          GP[i * LD + t] = vp;
-          GC[i * LD + t] = vc;
-        }
-#pragma unroll
-        for (int l = 0; l < 6; ++l) {
-          GP[(3 + l) * LD + t] = gl[l] * g.xip[kArm[l]];
-          GC[(3 + l) * LD + t] = gl[l] * g.xic[kArm[l]];
-        }
+        for (int l = 0; l < 6; ++l)
+          if (kLinkRecv[l] - 1 == i) {
+            vp = fma(-gl[l], g.xip[kArm[l]], vp);
+            vc = fma(-gl[l], g.xic[kArm[l]], vc);
+          }
+        GP[i * LD + t] = vp;
+        GC[i * LD + t] = vc;
       }
-      __syncthreads();
 #pragma unroll
-      for (int p = 0; p < 9; ++p) {
-        lo[p] = __builtin_amdgcn_readfirstlane(sh.lo[p]);
-        hi[p] = __builtin_amdgcn_readfirstlane(sh.hi[p]);
-        sh.f[p * LD + t] = (unsigned char)(f[p] - lo[p]);
+      for (int l = 0; l < 6; ++l) {
+        GP[(3 + l) * LD + t] = gl[l] * g.xip[kArm[l]];
+        GC[(3 + l) * LD + t] = gl[l] * g.xic[kArm[l]];
       }
+#pragma unroll
+      for (int p = 0; p < 9; ++p) U[p * LD + t] = u[p];
     }
-    int jlo = lo[0], jhi = hi[0], drift = 0, steps = 0;
+    const int pl = min(lane, 8);
+    int whi = sh.hi[0][pl];
+    wlo = sh.lo[0][pl];
+#pragma unroll
+    for (int w = 1; w < kFarrowBlock / 64; ++w) {
+      wlo = min(wlo, sh.lo[w][pl]);
+      whi = max(whi, sh.hi[w][pl]);
+    }
+    int jlo = 1 << 30, jhi = -(1 << 30), drift = 0, steps = 0;
 #pragma unroll
     for (int p = 0; p < 9; ++p) {
-      jlo = min(jlo, lo[p]);
-      jhi = max(jhi, hi[p]);
-      drift = max(drift, hi[p] - lo[p]);
-      if (t == p && steps + hi[p] - lo[p] < kFarrowSteps)
-        for (int i = 0; i <= hi[p] - lo[p]; ++i)
-          sh.step[steps + i] = FarrowStep{p * LD, lo[p] + i, i, 0};
-      steps += hi[p] - lo[p] + 1;
+      const int x = __builtin_amdgcn_readlane(wlo, p), y = __builtin_amdgcn_readlane(whi, p);
+      jlo = min(jlo, x);
+      jhi = max(jhi, y);
+      drift = max(drift, y - x);
+      steps += y - x + 1;
     }
-    if (t == 9 && steps <= kFarrowSteps)       // the list's end, and what is read ahead of it
-      sh.step[steps] = sh.step[steps + 1] = sh.step[steps + 2] = FarrowStep{0, 0, 0, 1};
     // One set of bases for all positions when they lie as close together as
     // the light times say (the host's `rows`); else one per position, and
     // fewer link samples where the positions themselves move too fast.
     const bool together = n + jhi - jlo <= kFarrowBlock;
+    const bool fast = together && drift == 0 && jhi - jlo <= kFarrowPad;
     if (n > 1 && (n + drift > kFarrowBlock || steps > kFarrowSteps)) {
       most = max(1, n / 2);
       __syncthreads();                         // lo, hi read before they are set again
       continue;
     }
-    __syncthreads();                           // f, step
+    if (!fast) {
+      int at = 0;
+#pragma unroll
+      for (int p = 0; p < 9; ++p) {
+        const int x = __builtin_amdgcn_readlane(wlo, p), y = __builtin_amdgcn_readlane(whi, p);
+        sh.f[p * kFarrowBlock + t] = (unsigned char)(f[p] - x);
+        if (t == p)
+          for (int i = 0; i <= y - x; ++i) sh.step[at + i] = FarrowStep{p, x + i, i, 0};
+        at += y - x + 1;
+      }
+      if (t == 9)                              // the list's end, and what is read ahead of it
+        sh.step[at] = sh.step[at + 1] = sh.step[at + 2] = FarrowStep{0, 0, 0, 1};
+    }
+    __syncthreads();                           // fractions, gradients, steps
 
     // B.
 #pragma unroll 1
     for (int g = 0; g < (together ? 1 : 9); ++g) {
       int base = jlo, nj = n + jhi - jlo;
       if (!together) {
-        base = __builtin_amdgcn_readfirstlane(sh.lo[g]);
-        nj = n + __builtin_amdgcn_readfirstlane(sh.hi[g]) - base;
+        base = __builtin_amdgcn_readlane(wlo, g);
+        nj = n + __builtin_amdgcn_readlane(whi, g) - base;
       }
       const int64_t j0 = q0 + base - (H - 1);  // h-index of window element 0
       double cp[D + 1], cc[D + 1], dp[D + 1], dc[D + 1];
@@ -209,45 +233,13 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
 #pragma unroll
       for (int m = 0; m <= D; ++m) dp[m] = dc[m] = 0.0;
       for (int e = lane; e < 2 * WR; e += 64) mine[e] = 0.0;
-      // Step by step, each step's LDS reads issued before the previous step's
-      // sums: the link sample r served by this base and its u and gradients,
-      // zero where this base serves none.
-      struct Item {
-        int at;
-        bool ok;
-        double u, gp, gc;
-      };
-      auto fetch = [&](const FarrowStep& st) {
-        Item it;
-        const int r = t + base - st.f, rc = min(max(r, 0), n - 1);
-        it.at = st.row + rc;
-        it.ok = r == rc && (int)sh.f[it.at] == st.k;
-        it.u = U[it.at];
-        it.gp = GP[it.at];
-        it.gc = GC[it.at];
-        return it;
-      };
-      auto uniform = [](const FarrowStep& v) {
-        return FarrowStep{__builtin_amdgcn_readfirstlane(v.row), __builtin_amdgcn_readfirstlane(v.f),
-                          __builtin_amdgcn_readfirstlane(v.k),
-                          __builtin_amdgcn_readfirstlane(v.end)};
-      };
-      int i = 0;
-      if (!together)
-        while (__builtin_amdgcn_readfirstlane(sh.step[i].row) != g * LD) ++i;
-      Item it = fetch(uniform(sh.step[i]));
-      FarrowStep nxt = uniform(sh.step[i + 1]), later = sh.step[i + 2];
-      i += 2;
-#pragma unroll 1
-      for (;;) {
-        const Item ahead = fetch(nxt);
-        const bool last = nxt.end || (!together && nxt.row != g * LD);
-        nxt = uniform(later);
-        later = sh.step[min(++i, kFarrowSteps + 2)];
-        const double u = it.ok ? it.u : 0.0;
-        const double gp = it.ok ? it.gp : 0.0, gc = it.ok ? it.gc : 0.0;
+      // a position's share of the coefficient gradients, and with SKY its
+      // values vp, vc and the derivative ds along its delay
+      auto serve = [&](double u, double gp, double gc, double& vp, double& vc, double& ds) {
         if constexpr (SKY) {
-          double vp = cp[D], vc = cc[D], wp = cp[D], wc = cc[D];   // w: derivative
+          double wp = cp[D], wc = cc[D];       // derivatives
+          vp = cp[D];
+          vc = cc[D];
 #pragma unroll
           for (int m = D - 1; m >= 0; --m) {
             vp = fma(vp, u, cp[m]);
@@ -257,11 +249,7 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
               wc = fma(wc, u, vc);
             }
           }
-          if (it.ok) {
-            U[it.at] = fma(gp, wp, gc * wc);
-            GP[it.at] = vp;
-            GC[it.at] = vc;
-          }
+          ds = fma(gp, wp, gc * wc);
         }
         dp[0] += gp;
         dc[0] += gc;
@@ -272,8 +260,80 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
           dc[m] = fma(gc, pw, dc[m]);
           if (m < D) pw *= u;
         }
-        it = ahead;
-        if (last) break;
+      };
+      if (fast) {
+        // base t serves link sample t + jlo - f of each position: before the
+        // run's first and after its last the gradients are zero.  The next
+        // position's LDS reads are issued before this one's sums.
+        int at = t + jlo - __builtin_amdgcn_readlane(wlo, 0);
+        double u = U[at], gp = GP[at], gc = GC[at];
+#pragma unroll 1
+        for (int p = 0; p < 9; ++p) {
+          const int q = min(p + 1, 8);
+          const int an = t + q * LD + jlo - __builtin_amdgcn_readlane(wlo, q);
+          const double un = U[an], gpn = GP[an], gcn = GC[an];
+          double vp, vc, ds;
+          serve(u, gp, gc, vp, vc, ds);
+          if constexpr (SKY) {
+            if ((unsigned)(at - p * LD) < (unsigned)n) {
+              U[at] = ds;
+              GP[at] = vp;
+              GC[at] = vc;
+            }
+          }
+          at = an;
+          u = un;
+          gp = gpn;
+          gc = gcn;
+        }
+      } else {
+        // Step by step, each step's LDS reads issued before the previous
+        // step's sums: the link sample r served by this base and its u and
+        // gradients, zero where this base serves none.
+        struct Item {
+          int at;
+          bool ok;
+          double u, gp, gc;
+        };
+        auto fetch = [&](const FarrowStep& st) {
+          Item it;
+          const int r = t + base - st.f, rc = min(max(r, 0), n - 1);
+          it.at = st.row * LD + rc;
+          it.ok = r == rc && (int)sh.f[st.row * kFarrowBlock + rc] == st.k;
+          it.u = U[it.at];
+          it.gp = GP[it.at];
+          it.gc = GC[it.at];
+          return it;
+        };
+        auto uniform = [](const FarrowStep& v) {
+          return FarrowStep{
+              __builtin_amdgcn_readfirstlane(v.row), __builtin_amdgcn_readfirstlane(v.f),
+              __builtin_amdgcn_readfirstlane(v.k), __builtin_amdgcn_readfirstlane(v.end)};
+        };
+        int i = 0;
+        if (!together)
+          while (__builtin_amdgcn_readfirstlane(sh.step[i].row) != g) ++i;
+        Item it = fetch(uniform(sh.step[i]));
+        FarrowStep nxt = uniform(sh.step[i + 1]), later = sh.step[i + 2];
+        i += 2;
+#pragma unroll 1
+        for (;;) {
+          const Item ahead = fetch(nxt);
+          const bool last = nxt.end || (!together && nxt.row != g);
+          nxt = uniform(later);
+          later = sh.step[min(++i, kFarrowSteps + 2)];
+          double vp, vc, ds;
+          serve(it.ok ? it.u : 0.0, it.ok ? it.gp : 0.0, it.ok ? it.gc : 0.0, vp, vc, ds);
+          if constexpr (SKY) {
+            if (it.ok) {
+              U[it.at] = ds;
+              GP[it.at] = vp;
+              GC[it.at] = vc;
+            }
+          }
+          it = ahead;
+          if (last) break;
+        }
       }
       // coefficient gradients -> gradients of the samples j0 + t + k, added to
       // the wave's own sums tap after tap (LDS adds of one wave keep their
