@@ -93,6 +93,11 @@ __device__ __forceinline__ void farrow_coefs(const double2* win, double (&p)[kFa
 #pragma unroll
       for (int j = 0; j < 16; ++j) w[j] = v[j];
     }
+    // computed here: sunk into a caller's branches, the sums would leave all
+    // rows loaded before them and spilled (adjoint with sky gradient of 3,155,760
+    // samples: 483 against 441 us)
+#pragma unroll
+    for (int j = 0; j <= D; ++j) asm volatile("" : "+v"(p[j]), "+v"(c[j]));
   } else {
 #pragma unroll
     for (int i = 0; i < H; ++i) {

@@ -19,10 +19,10 @@
 //
 // Bound by FP64 issue at two waves per SIMD (registers: 64 coefficients and
 // coefficient gradients per lane).  One year at dt = 10 s, order 25, against
-// nine weight sequences per link sample: with the sky gradient 804 -> 506 us,
+// nine weight sequences per link sample: with the sky gradient 804 -> 441 us,
 // without 380 -> 245 us (order 1: 191 -> 150; order 13: 272 -> 209).  With
 // predicates and a list of steps in phase B throughout, as where integer parts
-// cross within a run, 541 and 306 us.
+// cross within a run, it took 541 and 306 us where this took 506 and 245.
 #pragma once
 
 #include "batch_adjoint_kernels.hpp"
