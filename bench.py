@@ -64,8 +64,8 @@ def kernel_source_hash(names):
     return h.hexdigest()[:16]
 
 
-FUSED_SOURCES = ("device_common.hpp", "forward_kernels.hpp", "batch_kernels.hpp",
-                 "batch_types.hpp", "gb_device.hpp")
+FUSED_SOURCES = ("device_common.hpp", "forward_kernels.hpp", "farrow.hpp", "farrow_forward.hpp",
+                 "fir_tables.hpp", "batch_kernels.hpp", "batch_types.hpp", "gb_device.hpp")
 
 
 def recorded_traffic(name, sources):
@@ -185,13 +185,13 @@ def bench_headline(steps, warmup, keep):
     rate = 6.0 * n / (ms_step * 1e-3)
 
     group = tuned["group"]
-    ops = costs.lane_ops_fused_forward(bc.grids, bc.order, bc.generation, group)
+    ops = costs.kernel_ops_fused_forward(bc.grids, bc.order, bc.generation, bc.dt, group)
     nbytes = costs.batch_bytes(bc.grids, 3)
     traffic = recorded_traffic("fused_forward_batch512", FUSED_SOURCES)
     kernel = "fused_forward_kernel<26,2,%d,%d>" % (group, batch.tile // 2)
     roof = _roofline(ops, ms_launch, kernel, traffic, nbytes)
     roof["note"] = ("mean HIP-event time of the graph replay on the launch stream (the "
-                    "preparation kernel (work counter, sky trigonometry; a few us) and the fused "
+                    "filter-table kernel (~50 us) and the fused "
                     "kernel)")
 
     # keep what the CPU baseline compares: the sampled templates' inputs and
@@ -269,9 +269,9 @@ def bench_walkers(steps, warmup, keep, tdi_orbit_kind="rigid"):
     ms_adj = _timed(lambda: batch.adjoint_gb(params, g_out, g_params=g_par), steps, 1)
     n = bc.n_samples
     finite = bool(torch.isfinite(ll).all()) and bool(torch.isfinite(g_par).all())
-    ops = costs.lane_ops_fwd_adjoint(bc.grids, bc.order, bc.generation, tuned["group"], 2)
-    ops_adj = ops - costs.lane_ops_fused_forward(bc.grids, bc.order, bc.generation,
-                                                 tuned["group"])
+    ops_adj = costs.kernel_ops_adjoint(bc.grids, bc.order, bc.generation, bc.dt)
+    ops = ops_adj + costs.kernel_ops_fused_forward(bc.grids, bc.order, bc.generation, bc.dt,
+                                                   tuned["group"])
     nbytes = costs.fwd_adjoint_step_bytes_gb(bc.grids, 3)
     for k in keep:
         g = bc.grids[k]
@@ -325,27 +325,27 @@ def bench_single_template(steps):
     ms_tdi = _timed(tdi, steps, 2)
     ms_fwd = _timed(lambda: (proj(), tdi()), steps, 2)
     n = g.n_out
-    ops_tdi = costs.lane_ops_tdi(case.order, case.generation) * n
-    ops_proj = costs.lane_ops_projection(case.order) * g.n_y
+    ops_tdi = costs.kernel_ops_tdi(case.order, case.generation, g.dt) * n
+    ops_proj = costs.kernel_ops_projection(case.order) * g.n_y
     res = {"workload": case.name, "time_samples": n,
            "forward": {"value": 6.0 * n / (ms_fwd * 1e-3), "unit": UNIT, "ms": ms_fwd,
                        "step": "lr_project_links then lr_tdi_combine (TDI-2 XYZ+AET)"},
-           "roofline_tdi": _roofline(ops_tdi, ms_tdi, "tdi_kernel<26,2>",
+           "roofline_tdi": _roofline(ops_tdi, ms_tdi, "tdi_fir_kernel<26,2>",
                                      recorded_traffic("tdi_1yr", ("device_common.hpp",
-                                                                  "forward_kernels.hpp")),
+                                                                  "fir_tables.hpp",
+                                                                  "tdi_fir.hpp")),
                                      costs.tdi_bytes_per_sample(case.channels) * n),
-           "roofline_projection": _roofline(ops_proj, ms_proj, "project_links_kernel<26>", None,
+           "roofline_projection": _roofline(ops_proj, ms_proj, "farrow_project_kernel<26>", None,
                                             costs.projection_bytes_per_sample() * g.n_y)}
 
-    # the TDI adjoint alone (zero fill of g_y, then the scatter kernel)
+    # the TDI adjoint alone
     g_out = torch.randn(out.shape, dtype=torch.float64, device=dev,
                         generator=torch.Generator(device=dev).manual_seed(3))
     g_y = torch.empty_like(y)
     ms_tadj = _timed(lambda: native.tdi_adjoint(orb, t0_y, g.dt, g.n_y, case.generation,
                                                 case.order, case.channels, g.front_tdi, g_out,
                                                 g_y=g_y), steps, 2)
-    res["roofline_tdi_adjoint"] = _roofline(ops_tdi, ms_tadj, "tdi_adjoint_carry_kernel<26,2> "
-                                            "(with the zero fill of g_y)")
+    res["roofline_tdi_adjoint"] = _roofline(ops_tdi, ms_tadj, "tdi_fir_adjoint_kernel<26,2>")
     res["roofline_tdi_adjoint"]["over_forward_tdi"] = ms_tadj / ms_tdi
 
     # forward + likelihood + adjoint of the template (A/E/T rows)

@@ -162,11 +162,10 @@ int lr_tdi_combine(const lr_orbits *orb, double t0_y, double dt, int64_t n_y, co
  * Adjoints.  Not in the paper; they are the exact transposes of the linear
  * maps above (derived from Sec. IV.B-IV.C and the interpolation of
  * Sec. IV.E), so that a likelihood gradient can flow from the TDI channels
- * back to h+, hx and the sky angles.  Each wave of 128 sources sums its
- * scatters in a register carry in a fixed order, the waves of a tile are
- * summed in a fixed order, and every output element receives at most two
- * tile sums (added onto zero, which commutes): results are bitwise
- * reproducible.  Exception: when dt is so small against the light times that
+ * back to h+, hx and the sky angles.  The TDI transpose gathers through
+ * filters; the projection's sums a tile's gradients in a fixed order, and every
+ * output element receives at most two tile sums (added onto zero, which
+ * commutes): results are bitwise reproducible.  Exception: when dt is so small against the light times that
  * a wave's footprint does not fit LDS (about dt < L/50), LDS and global
  * atomics take over and results are reproducible to rounding only.
  * ---------------------------------------------------------------------- */

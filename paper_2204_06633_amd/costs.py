@@ -138,6 +138,55 @@ def lane_ops_fwd_adjoint(grids, order, generation, share_fwd, share_adj, sky=Tru
     return f + a
 
 
+# ---------------------------------------------------------------------------
+# The same per (template, sample) as the kernels compute it at dt of a second
+# and more: h+ and hx as polynomials of degree d = min(N - 1, 15) per stencil
+# base (mirrored pairs: (N / 2)(d + 1) + N operations per polarisation, then d
+# per position and polarisation), TDI as 12 filters of K taps with cubics in
+# time for weights (four operations per tap and filter, or four per weight,
+# shared by the templates of a work item, and one per template).  The functions
+# above count the textbook algorithm, which these undercut.
+# ---------------------------------------------------------------------------
+LIGHT_TIME = 8.4                                              # s, longest of the constellations
+
+
+def _coefficient_ops(order):
+    n = order + 1
+    return 2 * ((n // 2) * (min(order, 15) + 1) + n)
+
+
+def kernel_ops_projection(order):
+    return _coefficient_ops(order) + 9 * 2 * min(order, 15) + 320
+
+
+def kernel_ops_projection_adjoint(order, sky=True):
+    """Powers and sums per position, coefficient gradients back to samples; with
+    the sky gradient also the coefficients, values and derivatives, and the
+    geometry a second time."""
+    d = min(order, 15)
+    ops = _coefficient_ops(order) + 9 * (2 * (d + 1) + d - 1) + 320
+    return ops + (_coefficient_ops(order) + 9 * 4 * d + 420 if sky else 0)
+
+
+def kernel_ops_tdi(order, generation, dt, share=None):
+    """``share``: templates per weight in the fused forward; None: the plain
+    kernels, forward or transpose."""
+    s = -int(-(7 if generation == 2 else 3) * LIGHT_TIME // dt)
+    taps = (order + s + 1) & ~1
+    return 12 * taps * (4 if share is None else 1 + 4 / share)
+
+
+def kernel_ops_fused_forward(grids, order, generation, dt, share):
+    return sum(kernel_ops_projection(order) * g.n_y +
+               kernel_ops_tdi(order, generation, dt, share) * g.n_out
+               for g in grids if g.n_out > 0)
+
+
+def kernel_ops_adjoint(grids, order, generation, dt, sky=True):
+    return sum(kernel_ops_tdi(order, generation, dt) * g.n_out +
+               kernel_ops_projection_adjoint(order, sky) * g.n_y for g in grids if g.n_out > 0)
+
+
 def batch_bytes(grids, rows=3):
     """Algorithmic HBM bytes of a batched forward: read h+ and hx over each
     template's h range, write its channels."""
