@@ -52,9 +52,12 @@ struct FarrowShared {
 };
 
 // Doubles of dynamic LDS: u and the two gradients per position and link
-// sample, the window of h+ and hx, and the waves' sums.
-__host__ __device__ constexpr size_t farrow_adjoint_doubles(int N, bool window) {
-  return 27 * kFarrowLd + (window ? 2 * (kFarrowBlock + N) : 0) + (kFarrowBlock / 64) * 2 * (64 + N);
+// sample, the window of h+ and hx (wave: and of the phase's sine and cosine,
+// which the parameter sums use again: eight templates of a million samples 1.74
+// -> 1.71 ms), and the waves' sums.
+__host__ __device__ constexpr size_t farrow_adjoint_doubles(int N, bool window, bool wave) {
+  return 27 * kFarrowLd + ((window ? 2 : 0) + (wave ? 2 : 0)) * (kFarrowBlock + N) +
+         (kFarrowBlock / 64) * 2 * (64 + N);
 }
 
 template <int N, bool SKY, bool WAVE>
@@ -67,7 +70,9 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
   double* GP = U + 9 * LD;
   double* GC = U + 18 * LD;
   double2* win = reinterpret_cast<double2*>(lds + 27 * LD);
-  double* sums = lds + 27 * LD + (SKY ? 2 * (kFarrowBlock + N) : 0);
+  static_assert(SKY || !WAVE, "the window holds the waveform");
+  double2* trigs = win + kFarrowBlock + N;
+  double* sums = lds + 27 * LD + ((SKY ? 2 : 0) + (WAVE ? 2 : 0)) * (kFarrowBlock + N);
   double* mine = sums + wv * 2 * WR;
 
   load_sky(a.sky, sh.s_trig);
@@ -225,7 +230,10 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
         for (int k = t; k < nj + N - 1; k += kFarrowBlock) {
           int64_t j = j0 + k;
           j = j < 0 ? 0 : (j > a.n_h - 1 ? a.n_h - 1 : j);
-          win[k] = hs.at(j);
+          if constexpr (WAVE)
+            win[k] = hs.at(j, trigs[k]);
+          else
+            win[k] = hs.at(j);
         }
         __syncthreads();
         farrow_coefs<N>(win + min(t, nj - 1), cp, cc);
@@ -358,7 +366,9 @@ __device__ __forceinline__ void farrow_adjoint_tile(const ProjAdjArgs& a, int64_
         const int64_t j = j0 + e;
         if (j >= 0 && j < a.n_h) {
           if constexpr (WAVE) {
-            gb::adjoint_sums(hs.src, (double)(a.k0 + j) * a.dt, v[0], v[1], acc);
+            // the lane that filled this element of the window
+            const double2 sc = trigs[e];
+            gb::adjoint_sums(hs.src, (double)(a.k0 + j) * a.dt, sc.x, sc.y, v[0], v[1], acc);
           } else {
             atomicAdd(a.g_hp + j, v[0]);
             atomicAdd(a.g_hc + j, v[1]);
@@ -460,7 +470,7 @@ template <int N>
 hipError_t launch_farrow_adjoint(const ProjAdjArgs& a, hipStream_t s) {
   const int64_t blocks = (a.n_y + kFarrowRuns * a.rows - 1) / (kFarrowRuns * a.rows);
   const bool sky = a.sky_part != nullptr;
-  const size_t bytes = farrow_adjoint_doubles(N, sky) * sizeof(double);
+  const size_t bytes = farrow_adjoint_doubles(N, sky, false) * sizeof(double);
   if (sky) {
     const hipError_t e = allow_dynamic_lds(farrow_adjoint_kernel<N, true>, bytes);
     if (e != hipSuccess) return e;
@@ -476,7 +486,7 @@ hipError_t launch_farrow_adjoint(const ProjAdjArgs& a, hipStream_t s) {
 template <int N>
 hipError_t launch_batch_farrow_adjoint(const BatchAdjArgs& a, int64_t n_items, hipStream_t s) {
   const bool sky = a.sky_part != nullptr;
-  const size_t bytes = farrow_adjoint_doubles(N, sky) * sizeof(double);
+  const size_t bytes = farrow_adjoint_doubles(N, sky || a.params, a.params) * sizeof(double);
   const dim3 grid((unsigned)n_items), block(kFarrowBlock);
   hipError_t e = allow_dynamic_lds(batch_farrow_adjoint_kernel<N, true, true>, bytes);
   if (e == hipSuccess) e = allow_dynamic_lds(batch_farrow_adjoint_kernel<N, true, false>, bytes);

@@ -151,6 +151,12 @@ struct HSource {
     h.k0 = k0;
     return h;
   }
+  // waveform sample j, and its phase's sine and cosine
+  __device__ __forceinline__ double2 at(int64_t j, double2& trig) const {
+    double p, c;
+    gb::polarizations_at(src, ap0, ac0, (double)(k0 + j) * dt, p, c, trig.x, trig.y);
+    return make_double2(p, c);
+  }
   __device__ __forceinline__ double2 at(int64_t j) const {
     if (wave) {                                   // uniform
       double p, c;

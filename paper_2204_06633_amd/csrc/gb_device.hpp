@@ -48,14 +48,19 @@ __device__ __forceinline__ double phase(const Source& s, double t) {
   return kTwoPi * ((p - n) + rest) + s.phi0;
 }
 
-// h+ and hx at time t (ap0 = -(1 + cos^2 iota) A, ac0 = -2 cos(iota) A).
+// h+ and hx at time t (ap0 = -(1 + cos^2 iota) A, ac0 = -2 cos(iota) A), and the
+// phase's sine and cosine.
 __device__ __forceinline__ void polarizations_at(const Source& s, double ap0, double ac0, double t,
-                                                 double& hp, double& hc) {
-  double sn, cs;
+                                                 double& hp, double& hc, double& sn, double& cs) {
   sincos(phase(s, t), &sn, &cs);
   const double ap = ap0 * cs, ac = ac0 * sn;
   hp = s.c2 * ap - s.s2 * ac;
   hc = s.s2 * ap + s.c2 * ac;
+}
+__device__ __forceinline__ void polarizations_at(const Source& s, double ap0, double ac0, double t,
+                                                 double& hp, double& hc) {
+  double sn, cs;
+  polarizations_at(s, ap0, ac0, t, hp, hc, sn, cs);
 }
 
 // Seven sample sums of the parameter gradient (the transpose of the
@@ -65,11 +70,10 @@ __device__ __forceinline__ void polarizations_at(const Source& s, double ap0, do
 //   S0 += Gp a+ + Gc ax            (times 1/A: d/dA)
 //   S1 += d/d iota, S2 += d/d psi, S3 += Q (d/d phi0),
 //   S4 += Q t, S5 += Q t^2, S6 += Q t^3  (the phase polynomial's powers).
-__device__ __forceinline__ void adjoint_sums(const Source& s, double t, double g_p, double g_c,
-                                             double (&acc)[7]) {
+// sn, cs: sine and cosine of the phase at t.
+__device__ __forceinline__ void adjoint_sums(const Source& s, double t, double sn, double cs,
+                                             double g_p, double g_c, double (&acc)[7]) {
   const double A = s.A;
-  double sn, cs;
-  sincos(phase(s, t), &sn, &cs);
   const double Gp = g_p * s.c2 + g_c * s.s2;            // d/d a+
   const double Gc = -g_p * s.s2 + g_c * s.c2;           // d/d ax
   const double ap = -(1.0 + s.ci * s.ci) * A * cs, ac = -2.0 * s.ci * A * sn;
@@ -81,6 +85,12 @@ __device__ __forceinline__ void adjoint_sums(const Source& s, double t, double g
   acc[4] += Q * t;
   acc[5] += Q * t * t;
   acc[6] += Q * t * t * t;
+}
+__device__ __forceinline__ void adjoint_sums(const Source& s, double t, double g_p, double g_c,
+                                             double (&acc)[7]) {
+  double sn, cs;
+  sincos(phase(s, t), &sn, &cs);
+  adjoint_sums(s, t, sn, cs, g_p, g_c, acc);
 }
 
 // Gradient with respect to (A, f0, fdot, phi0, iota, psi) from the seven
