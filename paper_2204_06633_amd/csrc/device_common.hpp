@@ -45,9 +45,14 @@ __device__ __forceinline__ double spline_at(Seg seg, int series, double u) {
 
 // Spline series FIRST .. FIRST + COUNT - 1 at time tau.  When the whole wave
 // sits in one coarse segment (the usual case: a segment spans thousands of
-// samples) the coefficients are read once per wave with scalar loads instead
-// of once per lane.
-template <int FIRST, int COUNT>
+// samples) the coefficients are read once per wave instead of once per lane.
+// SCALAR: through an opaque pointer to constant memory, or the compiler joins
+// the two branches to one with loads by every lane.  Projection from polynomials of
+// 3,155,760 samples at order 25: 209 us joined, 200 with scalar loads; but the
+// kernels with a weight sequence per delay, which have no registers to spare,
+// spill more with them (TDI transpose of 1.6 million samples at order 31: 1413 us
+// joined, 1593 scalar).
+template <int FIRST, int COUNT, bool SCALAR = false>
 __device__ __forceinline__ void orbit_series(const OrbitView& o, double tau, double (&v)[COUNT]) {
   double s = floor(tau * o.inv_dt);
   s = fmin(fmax(s, 0.0), (double)(o.nseg - 1));
@@ -55,13 +60,17 @@ __device__ __forceinline__ void orbit_series(const OrbitView& o, double tau, dou
   const int si = (int)s;
   int su = __builtin_amdgcn_readfirstlane(si);
   if (__all(si == su)) {
-    // opaque, and constant memory: else the compiler joins the two branches
-    // to one with loads by every lane (the same projection: 209 against 200 us)
-    asm volatile("" : "+s"(su));
-    const auto seg = (const __attribute__((address_space(4))) double*)(o.coef +
-                                                                        (int64_t)su * kSegStride);
+    if constexpr (SCALAR) {
+      asm volatile("" : "+s"(su));
+      const auto seg = (const __attribute__((address_space(4))) double*)(o.coef +
+                                                                          (int64_t)su * kSegStride);
 #pragma unroll
-    for (int k = 0; k < COUNT; ++k) v[k] = spline_at(seg, FIRST + k, u);
+      for (int k = 0; k < COUNT; ++k) v[k] = spline_at(seg, FIRST + k, u);
+    } else {
+      const double* seg = o.coef + (int64_t)su * kSegStride;
+#pragma unroll
+      for (int k = 0; k < COUNT; ++k) v[k] = spline_at(seg, FIRST + k, u);
+    }
   } else {
     const double* seg = o.coef + (int64_t)si * kSegStride;
 #pragma unroll
@@ -134,10 +143,12 @@ struct LinkGeom {
   double xip[3], xic[3], kn[3];
 };
 
+// FAST: scalar orbit loads and the estimate's root, for kernels with the registers.
+template <bool FAST = true>
 __device__ __forceinline__ void link_geometry(const OrbitView& o, double tau, const Sky& sk,
                                               LinkGeom& g) {
   double v[15];
-  orbit_series<0, 15>(o, tau, v);
+  orbit_series<0, 15, FAST>(o, tau, v);
 #pragma unroll
   for (int s = 0; s < 3; ++s)
 #pragma unroll
@@ -152,7 +163,8 @@ __device__ __forceinline__ void link_geometry(const OrbitView& o, double tau, co
   for (int arm = 0; arm < 3; ++arm) {
     const int r = arm, e = (arm + 1) % 3;
     double d0 = g.x[r][0] - g.x[e][0], d1 = g.x[r][1] - g.x[e][1], d2 = g.x[r][2] - g.x[e][2];
-    const double inrm = fast_rsqrt(d0 * d0 + d1 * d1 + d2 * d2);
+    const double d2s = d0 * d0 + d1 * d1 + d2 * d2;
+    const double inrm = FAST ? fast_rsqrt(d2s) : 1.0 / sqrt(d2s);
     d0 *= inrm; d1 *= inrm; d2 *= inrm;
     g.n[arm][0] = d0; g.n[arm][1] = d1; g.n[arm][2] = d2;
     double un = sk.u[0] * d0 + sk.u[1] * d1 + sk.u[2] * d2;
