@@ -65,7 +65,8 @@ def kernel_source_hash(names):
 
 
 FUSED_SOURCES = ("device_common.hpp", "forward_kernels.hpp", "farrow.hpp", "farrow_forward.hpp",
-                 "fir_tables.hpp", "batch_kernels.hpp", "batch_types.hpp", "gb_device.hpp")
+                 "fir_tables.hpp", "batch_kernels.hpp", "batch_stream_kernels.hpp",
+                 "batch_types.hpp", "gb_device.hpp")
 
 
 def recorded_traffic(name, sources):

@@ -256,9 +256,11 @@ typedef struct {
     size_t off[24];      /* workspace region offsets (bytes) */
 } lr_batch;
 
-/* Device workspace bytes for a batch.  With adjoint != 0 it includes the
- * link-gradient scratch of lr_response_adjoint (6 values per link sample of
- * every template). */
+/* Device workspace bytes for a batch.  It holds the TDI filter tables of the
+ * forward where those are used, up to 60 bytes per output of the longest
+ * template (24 at order 25, dt = 10 s and LISA's arms: 76 MB for a year); with
+ * adjoint != 0 also the link-gradient scratch of lr_response_adjoint (6 values per
+ * link sample of every template). */
 size_t lr_batch_workspace(const lr_template *t, int64_t n, const lr_orbits *tdi, double dt,
                           int order, int generation, int channels, int group, int tile,
                           int segment, int adjoint);

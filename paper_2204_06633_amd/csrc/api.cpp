@@ -78,17 +78,23 @@ int farrow_rows(double L_max, double dt, int lanes, int most) {
   return s >= 2.0 && s <= most ? lanes - (int)s : lanes;
 }
 
-// The fused forward shares a filter weight between the templates of a work item
-// (operations per output and template in groups of two: 36 per tap, against
-// 129 N one by one in generation 2 and 55 N in generation 1).  Order 25, 32
-// templates: 1.5 million outputs at dt = 10 s 9.88 -> 6.40 ms; 200,000 outputs
-// at dt = 1.5 s 1.67 against 1.34 ms, at 1 s 1.77 against 1.68, at 0.7 s 1.82
-// against 1.98, where the rule takes one by one.  Its tables need LDS only
-// while they are built: 120 samples of delay keep that below 64 KB.
+// The fused forward shares a filter weight between the templates of a work item,
+// and its projection takes polynomials along.  Both cost by the tap, where the
+// kernel without them costs by the order: the line is the taps at which 32
+// templates of 60,000 outputs take the same time, for groups of one and two,
+// tiles of 512 and 1024, h from memory and synthesised (group 2, tile 512, us without
+// and with): generation 2, dt = 10 s, order 1 (8 taps) 140 and 132, order 25 (32)
+// 416 and 255; 5 s, order 1 (14) 142 and 150, order 3 (16) 225 and 165; 2.5 s,
+// order 7 (32) 283 and 238 (synthesised 250 and 253), order 25 (50) 484 and 363;
+// 1 s, order 25 (84) 533 and 529 (groups of one 554 and 669).  Generation 1, dt =
+// 10 s, order 1 (4) 111 and 130, order 7 (10) 158 and 155, order 25 (28) 295 and
+// 242; 5 s, order 7 (14) 156 and 178, order 13 (20) 209 and 204; 2.5 s, order 25
+// (36) 313 and 314.  The tables then take at most 60 bytes per output of the
+// longest template.
 FirShape fused_fir_shape(int order, int gen, double L_min, double L_max, double dt) {
   const FirShape f = fir_taps(order, gen, L_min, L_max, dt, 120.0);
   const int N = order + 1;
-  if (36.0 * f.taps + 150.0 > (gen == 1 ? 55.0 * N + 170.0 : 129.0 * N + 400.0)) return {0, 0};
+  if (gen == 1 ? order < 7 || 5 * f.taps > 6 * N + 16 : 5 * f.taps > 11 * N + 46) return {0, 0};
   return f;
 }
 

@@ -24,6 +24,7 @@ constexpr int64_t kAdjTile = 256;     // samples per adjoint work item (atomic k
 constexpr int64_t kCarryTile = 512;   // samples per work item of the carry adjoint kernels
 constexpr int64_t kFirOutputs = 512;  // outputs per TDI filter table
 constexpr int64_t kLikeChunk = 8192;  // elements per likelihood work item
+constexpr double kProjArm = 1.25;     // longest projection arms a fused run holds, in TDI arms
 
 enum Region {
   R_TPL, R_ITEMS, R_COUNTER, R_ADJ_TPL, R_TDI_ITEMS, R_PROJ_ITEMS, R_SKY_PART, R_SKY_SPAN,
@@ -77,31 +78,29 @@ struct FusedTile {
   int rows, samples, first;
   lr::FirShape fir;
 };
-FusedTile fused_tile(int tile, int halo, int order, int generation, const lr_orbits& tdi,
-                     double dt) {
+FusedTile fused_tile(int tile, int halo, const lr::FirShape& fir, double L_max, double dt) {
+  if (fir.taps == 0) return {0, tile, tile - halo, fir};
   FusedTile f;
   const int lanes = tile / 2;
   // A run is a workgroup's lanes minus the spread of the nine positions (2.01
-  // light times; the projection's orbits may have a quarter longer ones than
-  // the delays' before a run falls back to single stencils), in eights so that
+  // light times; kProjArm allows for the projection's orbits), in eights so that
   // a tile of two runs is whole rows of 16 lanes of output pairs.  Where that
-  // leaves a tile too few outputs next to its halo (dt below about 1 s), it
-  // takes more and emptier runs (32 templates of 200,000 outputs, order 25, dt =
-  // 0.5 s: 2375 us in two runs, 2069 in three); beyond that the runs read single
-  // stencils.
-  f.rows = lr::farrow_rows(1.25 * tdi.L_max, dt, lanes, lanes - 64);
-  f.samples = tile;
-  if (f.rows < lanes) {
-    f.rows = std::min(f.rows & ~7, lanes - 8);
-    if (8 * (2 * f.rows - halo) >= 7 * (tile - halo)) f.samples = 2 * f.rows;
-  }
-  // whole rows of 16 lanes where the filters serve: the lanes of a row share a
-  // table
-  f.fir = lr::fused_fir_shape(order, generation, tdi.L_min, tdi.L_max, dt);
-  f.first = f.samples - halo;
-  if (f.first < 32) f.fir = {0, 0};
-  if (f.fir.taps > 0) f.first &= ~31;
+  // leaves a tile too few outputs next to its halo (tiles of 256 at dt below about 2
+  // s), it takes more and emptier runs.
+  f.rows = std::min(lr::farrow_rows(kProjArm * L_max, dt, lanes, lanes - 64) & ~7, lanes - 8);
+  f.samples = 8 * (2 * f.rows - halo) >= 7 * (tile - halo) ? 2 * f.rows : tile;
+  // the lanes of a row share a table
+  f.first = (f.samples - halo) & ~31;
+  f.fir = fir;
   return f;
+}
+
+// The filters of a batch with these orbits: none where the projection's arms
+// are so much longer than the TDI's that its runs would not hold the positions.
+lr::FirShape batch_fir(int order, int generation, const lr_orbits& proj, const lr_orbits& tdi,
+                       double dt) {
+  if (!(proj.L_max <= kProjArm * tdi.L_max)) return {0, 0};
+  return lr::fused_fir_shape(order, generation, tdi.L_min, tdi.L_max, dt);
 }
 
 size_t fir_table_bytes(const lr::FirShape& fir) {
@@ -114,7 +113,7 @@ int64_t fir_intervals(const lr::FirShape& fir, int64_t max_n_out) {
 
 int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, int order,
               int generation, int channels, int group, int tile, int segment, int adjoint,
-              int64_t padj_tile, Plan& P) {
+              const lr_orbits& proj, int64_t padj_tile, Plan& P) {
   if (n < 0 || (n > 0 && !t)) return set_error(LR_E_ARG, "bad template list");
   if (group != 1 && group != 2 && group != 4)
     return set_error(LR_E_UNSUPPORTED, "group %d (1, 2 or 4 templates per work item)", group);
@@ -137,9 +136,13 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
     return set_error(LR_E_UNSUPPORTED, "dt = %g s is too small for the fused kernel (the TDI "
                                        "stencil needs %lld + %lld of %d link samples)",
                      dt, (long long)F, (long long)B, tile);
-  const FusedTile ft = fused_tile(tile, tile - P.T_out, order, generation, *tdi, dt);
+  // the tables' room depends on the TDI orbits alone: so does the workspace
+  P.fir = lr::fused_fir_shape(order, generation, tdi->L_min, tdi->L_max, dt);
+  const FusedTile ft = fused_tile(tile, tile - P.T_out,
+                                  batch_fir(order, generation, proj, *tdi, dt), tdi->L_max, dt);
+  // and the work list is sized for the filters' tiles, which are the smaller
+  const FusedTile most = fused_tile(tile, tile - P.T_out, P.fir, tdi->L_max, dt);
   P.T_first = ft.first;
-  P.fir = ft.fir;
   const int64_t rows = channels == LR_XYZ_AET ? 6 : 3;
 
   // grouped forward work list: longest templates first
@@ -160,7 +163,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
                                    order_idx[s]};
       gmax[g] = std::max(gmax[g], T.n_out);
     }
-    tiles1 += (gmax[g] + P.T_first - 1) / P.T_first;
+    tiles1 += (gmax[g] + most.first - 1) / most.first;
   }
   // Segments of K tiles carry the TDI halo from tile to tile (every tile
   // after the first has as many outputs as link samples) when the halo fits the kernel's
@@ -172,14 +175,17 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
   // fused kernel relies on it (an item without a tile would skip the barrier
   // that orders the reads of the item index before the next fetch).
   const int64_t seg_out = P.T_first + (int64_t)(P.K - 1) * ft.samples;
+  const int64_t seg_least = most.first + (int64_t)(P.K - 1) * most.samples;
+  int64_t most_items = 0;
   for (int64_t g = 0; g < n_groups; ++g) {
+    most_items += (gmax[g] + seg_least - 1) / seg_least;
     const int64_t segs = (gmax[g] + seg_out - 1) / seg_out;
     for (int64_t sg = 0; sg < segs; ++sg) {
       P.items.push_back((int)g);
       P.items.push_back((int)sg);
     }
   }
-  if ((int64_t)P.items.size() / 2 > (int64_t)0x7fffffff)
+  if (most_items > (int64_t)0x7fffffff)
     return set_error(LR_E_ARG, "too many work items");
 
   // adjoint and likelihood lists, caller's order
@@ -251,7 +257,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
   }
 
   P.bytes[R_TPL] = P.tpl.size() * sizeof(lr::BatchTemplate);
-  P.bytes[R_ITEMS] = P.items.size() * sizeof(int);
+  P.bytes[R_ITEMS] = (size_t)most_items * 2 * sizeof(int);
   P.bytes[R_COUNTER] = sizeof(int);
   P.bytes[R_ADJ_TPL] = P.adj.size() * sizeof(lr::BatchAdjTemplate);
   P.bytes[R_TDI_ITEMS] = adjoint ? P.tdi_items.size() * sizeof(int64_t) : 0;
@@ -321,8 +327,8 @@ int launch_forward(const lr_batch* b, const double* hp, const double* hc, const 
   a.inv_dt = 1.0 / b->dt;
   a.F = b->front;
   a.halo = b->tile - b->tile_out;
-  const FusedTile ft = fused_tile(b->tile, a.halo, b->order, b->generation, b->tdi, b->dt);
-  const lr::FirShape& fir = ft.fir;
+  const lr::FirShape fir = batch_fir(b->order, b->generation, b->proj, b->tdi, b->dt);
+  const FusedTile ft = fused_tile(b->tile, a.halo, fir, b->tdi.L_max, b->dt);
   a.rows = ft.rows;
   a.samples = ft.samples;
   a.T_out = ft.first;
@@ -339,8 +345,8 @@ int launch_forward(const lr_batch* b, const double* hp, const double* hc, const 
   a.n_templates = b->n_templates;
   a.fir = at<double>(b, R_FIR);
   a.fir_split = at<int>(b, R_FIR_SPLIT);
-  a.n_fir = (int64_t)((b->off[R_FIR_SPLIT] - b->off[R_FIR]) /
-                      std::max<size_t>(1, fir_table_bytes(fir)));
+  a.n_fir = fir.taps > 0 ? (int64_t)((b->off[R_FIR_SPLIT] - b->off[R_FIR]) / fir_table_bytes(fir))
+                         : 0;
   a.fir_lo = fir.lo;
   a.fir_k = fir.taps;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -384,7 +390,7 @@ size_t lr_batch_workspace(const lr_template* t, int64_t n, const lr_orbits* tdi,
                           int segment, int adjoint) {
   Plan P;
   if (make_plan(t, n, tdi, dt, order, generation, channels, group, tile, segment, adjoint,
-                kPadjTileMin, P))
+                tdi ? *tdi : lr_orbits{}, kPadjTileMin, P))
     return 0;
   return P.total;
 }
@@ -398,7 +404,7 @@ int lr_batch_prepare(const lr_template* t, int64_t n, const lr_orbits* proj,
   if (!std::isfinite(t0) || !(dt > 0.0) || !std::isfinite(dt)) return set_error(LR_E_ARG, "bad t0 or dt");
   Plan P;
   if (int st = make_plan(t, n, tdi, dt, order, generation, channels, group, tile, segment,
-                         adjoint, padj_tile(proj->L_max, dt), P))
+                         adjoint, *proj, padj_tile(proj->L_max, dt), P))
     return st;
   if (!ws || ws_bytes < P.total)
     return set_error(LR_E_WORKSPACE, "workspace %zu bytes < %zu", ws_bytes, P.total);
@@ -438,7 +444,8 @@ int lr_batch_prepare(const lr_template* t, int64_t n, const lr_orbits* proj,
     if (P.bytes[r]) std::memcpy(img.data() + P.off[r], src, P.bytes[r]);
   };
   put(R_TPL, P.tpl.data());
-  put(R_ITEMS, P.items.data());
+  if (!P.items.empty())
+    std::memcpy(img.data() + P.off[R_ITEMS], P.items.data(), P.items.size() * sizeof(int));
   put(R_ADJ_TPL, P.adj.data());
   put(R_TDI_ITEMS, P.tdi_items.data());
   put(R_PROJ_ITEMS, P.proj_items.data());

@@ -9,137 +9,19 @@
 //      -- the link series never reaches HBM;
 //   2. evaluates TDI (Sec. IV.C) for all M templates at once: the delays
 //      depend on the orbits only, so each filter weight (fir_tables.hpp), or
-//      each Lagrange coefficient sequence where the filters do not serve, is
-//      formed once per sample and applied to the M templates' series;
+//      each Lagrange coefficient sequence in an interval that no filter serves,
+//      is formed once per sample and applied to the M templates' series;
 //   3. stores X/Y/Z and/or A/E/T of each template.
+// Batches without filters (fused_fir_shape) run stream_forward_kernel instead.
 #pragma once
 
-#include "batch_types.hpp"
+#include "batch_stream_kernels.hpp"
 #include "farrow_forward.hpp"
 #include "fir_tables.hpp"
 
 namespace lr {
 
-// TDI of the lane's two outputs for M templates from their LDS link windows
-// (rows of YT link samples).
-template <int N, int GEN, int M, int YT>
-__device__ __forceinline__ void fused_tdi(const BatchFwdArgs& a, const double* ylds,
-                                          const double (&La)[6], const double (&Lb)[6], int c0,
-                                          const bool (&live)[M], double (&acc)[M][2][3]) {
-  constexpr int H = N / 2;
-  constexpr int ND = TdiTab<GEN>::v.ndirect;
-  const GroupTable<GEN>& GT = group_table<GEN>();
-  // delayed terms accumulate unscaled streams; the undelayed ones are added
-  // after the scale, at the end
-#pragma unroll
-  for (int k = 0; k < M; ++k)
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc[k][s][c] = 0.0;
-  // The padding bound keeps every stored output's stencil inside the tile;
-  // the clamp only guards the idle lanes past a template's end.
-  const int top = YT - 1 - N;
-  auto stencil = [&](const GroupRow& G, double& ea, double& eb, bool& same, int& ja, int& jb) {
-    const int sa = split_delay(row_delay(G, La), a.inv_dt, ea);
-    const int sb = split_delay(row_delay(G, Lb), a.inv_dt, eb);
-    same = __all(sa == sb);
-    ja = min(max(c0 + sa - (H - 1), 0), top);
-    jb = min(max(c0 + 1 + sb - (H - 1), 0), top);
-  };
-  // rows that feed one channel c (see GroupTable): one FMA per template and
-  // sample; a two-link group of one channel interpolates the signed sum of
-  // its link series
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-#pragma unroll 1
-    for (int g = GT.first[c]; g < GT.comb[c]; ++g) {
-      const GroupRow& G = GT.row[g];
-      double ea, eb;
-      bool same;
-      int ja, jb;
-      stencil(G, ea, eb, same, ja, jb);
-      const double* w[M];
-#pragma unroll
-      for (int k = 0; k < M; ++k) w[k] = ylds + (k * 6 + G.link[0]) * YT;
-      double xa[M], xb[M];
-      stream_series<N, YT, M>(ea, eb, same, [&w](int s, int i) { return w[s][i]; },
-                              ParStream<YT>(ja), jb, xa, xb);
-#pragma unroll
-      for (int k = 0; k < M; ++k) {
-        acc[k][0][c] = fma(G.sign, xa[k], acc[k][0][c]);
-        acc[k][1][c] = fma(G.sign, xb[k], acc[k][1][c]);
-      }
-    }
-#pragma unroll 1
-    for (int g = GT.comb[c]; g < GT.first[c + 1]; ++g) {
-      const GroupRow& G = GT.row[g];
-      double ea, eb;
-      bool same;
-      int ja, jb;
-      stencil(G, ea, eb, same, ja, jb);
-      const double* w0[M];
-      const double* w1[M];
-#pragma unroll
-      for (int k = 0; k < M; ++k) {
-        w0[k] = ylds + (k * 6 + G.link[0]) * YT;
-        w1[k] = ylds + (k * 6 + G.link[1]) * YT;
-      }
-      const double q = G.ratio;
-      double xa[M], xb[M];
-      stream_series<N, YT, M>(ea, eb, same,
-                              [&w0, &w1, q](int s, int i) { return fma(q, w1[s][i], w0[s][i]); },
-                              ParStream<YT>(ja), jb, xa, xb);
-#pragma unroll
-      for (int k = 0; k < M; ++k) {
-        acc[k][0][c] = fma(G.sign, xa[k], acc[k][0][c]);
-        acc[k][1][c] = fma(G.sign, xb[k], acc[k][1][c]);
-      }
-    }
-  }
-  // two-link groups whose uses feed different channels
-#pragma unroll 1
-  for (int g = GT.first[3]; g < GT.n; ++g) {
-    const GroupRow& G = GT.row[g];
-    double ea, eb;
-    bool same;
-    int ja, jb;
-    stencil(G, ea, eb, same, ja, jb);
-    const double* w[2 * M];
-#pragma unroll
-    for (int k = 0; k < M; ++k) {
-      w[2 * k] = ylds + (k * 6 + G.link[0]) * YT;
-      w[2 * k + 1] = ylds + (k * 6 + G.link[1]) * YT;
-    }
-    double xa[2 * M], xb[2 * M];
-    stream_multi<N, YT, 2 * M>(ea, eb, same, w, ParStream<YT>(ja), jb, xa, xb);
-#pragma unroll
-    for (int k = 0; k < M; ++k)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        acc[k][0][c] = fma(G.sgn[0][c], xa[2 * k], fma(G.sgn[1][c], xa[2 * k + 1], acc[k][0][c]));
-        acc[k][1][c] = fma(G.sgn[0][c], xb[2 * k], fma(G.sgn[1][c], xb[2 * k + 1], acc[k][1][c]));
-      }
-  }
-#pragma unroll
-  for (int k = 0; k < M; ++k) {
-    double dir[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-    static_for<ND>([&](auto t) {
-      constexpr Direct dr = TdiTab<GEN>::v.direct[decltype(t)::value];
-      const double* w = ylds + (k * 6 + dr.link) * YT;
-      dir[0][dr.chan] += (double)dr.sign * w[par<YT>(c0)];
-      dir[1][dr.chan] += (double)dr.sign * w[par<YT>(c0 + 1)];
-    });
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        acc[k][s][c] = fma(LagrangeStream<N>::kScale, acc[k][s][c], dir[s][c]);
-  }
-  (void)live;
-}
-
-// The same from the filters: W the lane's position in its interval's table
+// TDI of the lane's two outputs for M templates from the filters: W the lane's position in its interval's table
 // (its DPP row's 16 coefficients), j0 the row element of its first output's
 // first tap, t, u powers of the two outputs' times in the interval.  A weight
 // is computed once and applied to the M templates: 12 K (4 + M) / M
@@ -208,18 +90,11 @@ __device__ __forceinline__ void fused_tdi_fir(const double* ylds, const double2*
   });
 }
 
-// Minimum resident waves per SIMD for the fused kernel's register budget
-// (build-time tuning knob).  Two: LDS lets no more workgroups of the usual
-// shapes share a CU, and the projection's coefficients need the registers.
-#ifndef LR_FUSED_MIN_WAVES
-#define LR_FUSED_MIN_WAVES 2
-#endif
-
 // WAVE: h+ / hx synthesised from each template's parameter row (Sec. III)
 // instead of read from the caller's arrays.  A compile-time choice: with the
 // waveform code in the same kernel the array path's registers spill.
 template <int N, int GEN, int M, int BLOCK, bool WAVE>
-__global__ __launch_bounds__(BLOCK, LR_FUSED_MIN_WAVES)
+__global__ __launch_bounds__(BLOCK, 2)
 void fused_forward_kernel(BatchFwdArgs a) {
   constexpr int HPX = fused_halo_cap(M, BLOCK);       // halo a row can carry
   constexpr int YR = kPerLane * BLOCK + HPX;          // row length
@@ -317,7 +192,7 @@ void fused_forward_kernel(BatchFwdArgs a) {
       // 2. TDI of the tile's outputs for all live templates
       // tile-relative output of sample a; a row of 16 lanes starts at a multiple
       // of 32 outputs, so that it lies in one interval of the filters
-      const int oa = 2 * tid - (a.fir_k > 0 ? (int)(o0 & 31) : 0);
+      const int oa = 2 * tid - (int)(o0 & 31);
       const bool out_a = oa >= 0 && oa < cnt;
       const int ob = max(0, min(oa, cnt - 2));        // idle lanes mirror the ends
       double acc[M][2][3];
@@ -325,7 +200,7 @@ void fused_forward_kernel(BatchFwdArgs a) {
       // stencils: such segments interpolate the delays one by one, like the
       // intervals that no filter serves.
       bad = __syncthreads_or(bad);
-      bool split = a.fir_k == 0 || bad;
+      bool split = bad;
       if (!split) {
         // outputs past the longest template of the batch have no interval, and
         // are not stored
@@ -347,13 +222,12 @@ void fused_forward_kernel(BatchFwdArgs a) {
         for (int i = q0; i <= q1; ++i) split |= a.fir_split[i] != 0;
       }
       if (split) {                                    // uniform
-        const bool all = a.fir_k == 0 || bad;
         double La[6], Lb[6], one[M][2][3];
         light_times(a.orb_t, a.t_off_t + (double)(o0 + ob) * a.dt, La);
         light_times(a.orb_t, a.t_off_t + (double)(o0 + ob + 1) * a.dt, Lb);
-        fused_tdi<N, GEN, M, YR>(a, ylds, La, Lb, a.F + ro + ob, live, one);
+        fused_tdi<N, GEN, M, YR, false>(a, ylds, La, Lb, a.F + ro + ob, live, one);
         const bool mine =
-            all || a.fir_split[min((o0 + ob) / kFirInterval, a.n_fir - 1)] != 0;
+            bad || a.fir_split[min((o0 + ob) / kFirInterval, a.n_fir - 1)] != 0;
 #pragma unroll
         for (int k = 0; k < M; ++k)
 #pragma unroll
@@ -395,19 +269,26 @@ void fused_forward_kernel(BatchFwdArgs a) {
 
 template <int N, int GEN, int M, int BLOCK, bool WAVE>
 hipError_t launch_fused_forward(const BatchFwdArgs& a, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL((fused_forward_kernel<N, GEN, M, BLOCK, WAVE>), dim3(blocks), dim3(BLOCK),
-                     0, s, a);
+  if (a.fir_k > 0)
+    hipLaunchKernelGGL((fused_forward_kernel<N, GEN, M, BLOCK, WAVE>), dim3(blocks), dim3(BLOCK),
+                       0, s, a);
+  else
+    hipLaunchKernelGGL((stream_forward_kernel<N, GEN, M, BLOCK, WAVE>), dim3(blocks), dim3(BLOCK),
+                       0, s, a);
   return hipGetLastError();
 }
 
-// Resident workgroups per CU of the fused kernel (sizes the persistent grid).
+// Resident workgroups per CU (sizes the persistent grid), of the roomier of the
+// two kernels: a workgroup that starts late finds the work list drained.
 template <int N, int GEN, int M, int BLOCK, bool WAVE>
 int fused_occupancy() {
-  int nb = 0;
+  int f = 0, t = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, fused_forward_kernel<N, GEN, M, BLOCK, WAVE>, BLOCK, 0) != hipSuccess)
-    nb = 1;
-  return nb > 0 ? nb : 1;
+          &f, fused_forward_kernel<N, GEN, M, BLOCK, WAVE>, BLOCK, 0) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &t, stream_forward_kernel<N, GEN, M, BLOCK, WAVE>, BLOCK, 0) != hipSuccess)
+    return 1;
+  return f > t ? (f > 0 ? f : 1) : (t > 0 ? t : 1);
 }
 
 #define LR_INSTANTIATE_BATCH_FWD_M(NT, GEN, M, BLOCK, WAVE)                              \

@@ -40,7 +40,7 @@ struct BatchFwdArgs {
   double t_off_p, t_off_t;   // time of output sample 0 minus each orbit grid's first sample
   double dt, inv_dt;
   int F;                     // link samples before the first output of a tile
-  int rows, samples;         // link samples per run of the projection and per tile
+  int rows, samples;         // link samples per run of the projection (filters) and per tile
   int T_out;                 // outputs of a segment's first tile (even): at most link samples
                              // per tile minus the TDI halo
   int halo;                  // TDI halo: padding before and after, rounded up to even
@@ -55,8 +55,8 @@ struct BatchFwdArgs {
   int64_t n_templates;
   // TDI filters, one table per interval of outputs (fir_tables.hpp): taps
   // o + fir_lo .. + fir_k - 1 of output o; split[q]: interval q needs the
-  // delays interpolated one by one; fir_k 0: all do, and run_forward_prep
-  // fills trig
+  // delays interpolated one by one; fir_k 0: the kernel without filters or
+  // polynomials (batch_stream_kernels.hpp), and run_forward_prep fills trig
   double* fir;               // [n_fir][6 links][fir_quads(fir_k)][16][2]
   int* fir_split;            // [n_fir]
   int64_t n_fir;

@@ -78,12 +78,15 @@ hipError_t run_project_adjoint(int order, const ProjAdjArgs& a, hipStream_t s) {
 hipError_t run_fused_forward(int order, int gen, int group, int tile, bool wave,
                              const BatchFwdArgs& a, int blocks, hipStream_t s) {
   // the kernel's rows hold at most fused_halo_cap(group, workgroup) carried
-  // samples, and a segment of one tile carries none
+  // samples, and a segment of one tile carries none; the filters need whole
+  // rows of 16 lanes of output pairs, and room for a row's shift in the tile
   if (a.seg_tiles < 1 || a.HP < 0 || a.HP > fused_halo_cap(group, tile / 2) ||
       (a.seg_tiles > 1) != (a.HP > 0) || (a.HP > 0 && a.HP != a.halo) || a.T_out < 2 ||
-      a.rows < 1 || a.rows > tile / 2 || a.samples > tile || a.T_out + a.halo > a.samples ||
-      (a.fir_k > 0 && (a.T_out % 32 != 0 || a.samples % 16 != 0 ||
-                       (a.samples % 32 != 0 && a.samples > tile - 16))))
+      a.samples > tile || a.T_out + a.halo > a.samples)
+    return hipErrorInvalidValue;
+  if (a.fir_k > 0 ? a.rows < 1 || a.rows > tile / 2 || a.T_out % 32 != 0 || a.samples % 16 != 0 ||
+                        (a.samples % 32 != 0 && a.samples > tile - 16)
+                  : a.samples != tile || a.T_out + a.halo != tile)
     return hipErrorInvalidValue;
   if (a.fir_k > 0) {
     hipError_t e = hipErrorInvalidValue;

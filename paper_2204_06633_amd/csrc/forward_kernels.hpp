@@ -30,18 +30,9 @@
 
 namespace lr {
 
-// Switches of kernels that are no more; lr_build_config() still reports them.
-#ifndef LR_PROJ_PIPE
-#define LR_PROJ_PIPE 2
-#endif
+// Switch of a kernel that is no more; lr_build_config() still reports it.
 #ifndef LR_PROJ_MIN_WAVES
 #define LR_PROJ_MIN_WAVES 1
-#endif
-#ifndef LR_FUSED2_MIN_WAVES
-#define LR_FUSED2_MIN_WAVES 3
-#endif
-#ifndef LR_FUSED2W_MIN_WAVES
-#define LR_FUSED2W_MIN_WAVES 2
 #endif
 
 constexpr int kBlock = kTile;          // lanes per workgroup
@@ -309,7 +300,7 @@ __device__ __forceinline__ void group_delay_bounds(const double (&L)[6], int cha
 // position, otherwise it starts at element jb0.  One LagrangePair serves all
 // S series of both samples.  Returns the streams' unscaled values
 // (LagrangeStream<N>::finish scales).
-template <int N, int CAP, int S, class Load>
+template <int N, int CAP, int S, bool ROLL = false, class Load>
 __device__ __forceinline__ void stream_series(double ea, double eb, bool same, const Load& load,
                                               const ParStream<CAP>& sa_, int jb0,
                                               double (&xa)[S], double (&xb)[S]) {
@@ -335,27 +326,33 @@ __device__ __forceinline__ void stream_series(double ea, double eb, bool same, c
     }
   } else {
     const ParStream<CAP> sb_(jb0);             // only here: most waves take `same`
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
+    auto tap = [&](int k) {
       P.tap(k);
 #pragma unroll
       for (int s = 0; s < S; ++s) {
         xa[s] = P.step_a(xa[s], load(s, sa_.at(k)), k);
         xb[s] = P.step_b(xb[s], load(s, sb_.at(k)), k);
       }
+    };
+    if constexpr (ROLL) {
+#pragma unroll 1
+      for (int k = 0; k < N; ++k) tap(k);
+    } else {
+#pragma unroll
+      for (int k = 0; k < N; ++k) tap(k);
     }
   }
 }
 
 // S series from parity-split LDS rows w[s] (measured links, possibly of
 // several templates).
-template <int N, int CAP, int S>
+template <int N, int CAP, int S, bool ROLL = false>
 __device__ __forceinline__ void stream_multi(double ea, double eb, bool same,
                                              const double* const (&w)[S],
                                              const ParStream<CAP>& sa_, int jb0,
                                              double (&xa)[S], double (&xb)[S]) {
-  stream_series<N, CAP, S>(ea, eb, same, [&w](int s, int i) { return w[s][i]; }, sa_, jb0, xa,
-                           xb);
+  stream_series<N, CAP, S, ROLL>(ea, eb, same, [&w](int s, int i) { return w[s][i]; }, sa_, jb0,
+                                 xa, xb);
 }
 
 // Global-memory version for one sample (clamped indices).
