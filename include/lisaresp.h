@@ -62,7 +62,7 @@ const char *lr_status_str(int status);
 const char *lr_last_error(void);
 /* ABI version of this header (bumped on incompatible changes); the library
  * returns the version it was built with. */
-#define LR_ABI_VERSION 5
+#define LR_ABI_VERSION 6
 int lr_abi_version(void);
 /* The build-time tuning switches the library was compiled with, as
  * "NAME=value;NAME=value;..." (register budgets, load pipelining, the TDI
@@ -85,6 +85,10 @@ typedef struct {
     const void *coef;    /* device storage written by lr_orbits_init */
     double L_min, L_max; /* rigorous bounds of the light-time splines (s) */
     double R_max;        /* rigorous bound of |x| over the position splines (m) */
+    double L_rate;       /* rigorous bound of |dL/dt| over the light-time splines (s/s) */
+    double L_jump;       /* largest jump of a light-time spline's cubic coefficient
+                            at a knot (s/s^3): with L_rate, how smooth the light times
+                            are, which decides how the TDI calls interpolate */
 } lr_orbits;
 
 /* Bytes of device storage lr_orbits_init needs for n coarse samples. */
@@ -99,10 +103,10 @@ int lr_orbits_init(double t0, double dt, int64_t n, const double *x_sc, const do
                    void *d_storage, size_t bytes, lr_orbits *out, void *stream);
 
 /* [host only] The same spline fit without a device: fills `out` with t0, dt,
- * n and the bounds L_min, L_max, R_max (coef = NULL), which is all that
- * lr_projection_padding and lr_tdi_padding read -- so a caller can size its
- * padded buffers before anything is allocated or uploaded.  The handle is
- * not valid for the compute calls.  Errors: LR_E_ARG as lr_orbits_init. */
+ * n and the bounds (coef = NULL), which is all that lr_projection_padding and
+ * lr_tdi_padding read -- so a caller can size its padded buffers before
+ * anything is allocated or uploaded.  The handle is not valid for the compute
+ * calls.  Errors: LR_E_ARG as lr_orbits_init. */
 int lr_orbits_bounds(double t0, double dt, int64_t n, const double *x_sc, const double *ltt,
                      lr_orbits *out);
 

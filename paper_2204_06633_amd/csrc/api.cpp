@@ -53,15 +53,33 @@ int carry_row_capacity(int order, double spread, double dt, int rows, int ncarry
 // forward 232 against 535, adjoint 260 against 842; generation 1 forward 202
 // against 254; 32,768 samples of generation 2 20.8 against 40.8.  At dt = 2 s
 // the taps outgrow N and low orders and generation 1 stay with the streams.
-static FirShape fir_taps(int order, int gen, double L_min, double L_max, double dt, double most) {
-  const double s = std::ceil((gen == 1 ? 3 : 7) * L_max / dt);
-  if (!(L_min > 0.0) || !(s < most)) return {0, 0};
-  return {-(int)s - ((order + 1) / 2 - 1), (order + (int)s + 1) & ~1};
+//
+// They also need light times that one cubic per tap follows over a tile and what
+// reaches it (512 outputs and the taps): a delay that changes by at most 2.4e-4 of
+// a sample -- the cubic through four Chebyshev nodes errs by (pi change / 2)^4 /
+// 192 of the series at worst, at the Nyquist frequency: 1e-16 -- and knots that
+// leave the splines within rounding of one cubic.  A jump of J in the third-degree
+// coefficient moves the cubic through the nodes by at most 0.048 J h^3 over
+// an interval of half width h.  Elsewhere a tile would fall into pieces that cost as
+// much as a tile each: Keplerian orbits sampled every 1000 s (their light times
+// carry 1e-13 s of rounding from positions of 1e11 m, and the splines follow it),
+// 300,000 outputs at order 25 and dt = 10 s: 79 us one by one, 184 in pieces; every
+// 100 s 79 and 1236; every 10,000 s, where nothing splits, 79 and 39.
+static FirShape fir_taps(int order, int gen, const LightTimes& L, double dt, double most) {
+  const int chain = gen == 1 ? 3 : 7;
+  const double s = std::ceil(chain * L.max / dt);
+  if (!(L.min > 0.0) || !(s < most)) return {0, 0};
+  const int taps = (order + (int)s + 1) & ~1;
+  const double w = 512.0 + taps, h = 0.5 * w * dt;
+  const double change = chain * L.rate * w;
+  const double bend = chain * 0.048 * (std::floor(w * dt / L.knot) + 1.0) * L.jump * h * h * h / dt;
+  if (!(change <= 2.4e-4) || !(bend <= 1e-14 + 2e-15 * chain * L.min / dt)) return {0, 0};
+  return {-(int)s - ((order + 1) / 2 - 1), taps};
 }
 
-FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt, int64_t n,
+FirShape tdi_fir_shape(int order, int gen, const LightTimes& L, double dt, int64_t n,
                        bool adjoint) {
-  const FirShape f = fir_taps(order, gen, L_min, L_max, dt, 40.0);
+  const FirShape f = fir_taps(order, gen, L, dt, 40.0);
   // {intercept, slope}: filters, one by one in generation 1 and 2
   constexpr double fwd[2][6] = {{8.5, 0.38, 12.0, 0.31, 20.0, 0.68},
                                 {33.0, 6.2, 66.0, 7.4, 85.0, 17.6}};
@@ -91,8 +109,8 @@ int farrow_rows(double L_max, double dt, int lanes, int most) {
 // 242; 5 s, order 7 (14) 156 and 178, order 13 (20) 209 and 204; 2.5 s, order 25
 // (36) 313 and 314.  The tables then take at most 60 bytes per output of the
 // longest template.
-FirShape fused_fir_shape(int order, int gen, double L_min, double L_max, double dt) {
-  const FirShape f = fir_taps(order, gen, L_min, L_max, dt, 120.0);
+FirShape fused_fir_shape(int order, int gen, const LightTimes& L, double dt) {
+  const FirShape f = fir_taps(order, gen, L, dt, 120.0);
   const int N = order + 1;
   if (gen == 1 ? order < 7 || 5 * f.taps > 6 * N + 16 : 5 * f.taps > 11 * N + 46) return {0, 0};
   return f;
@@ -270,7 +288,7 @@ int fit_orbits(double t0, double dt, int64_t n, const double* x_sc, const double
   for (int l = 0; l < 6; ++l)
     fit_not_a_knot(ltt + l, 6, n, dt, coef.data() + 4 * (9 + l), lr::kSegStride);
 
-  double rmax = 0.0, lmax = -INFINITY, lmin = INFINITY;
+  double rmax = 0.0, lmax = -INFINITY, lmin = INFINITY, rate = 0.0, jump = 0.0;
   for (int64_t k = 0; k < nseg; ++k) {
     const double* seg = coef.data() + k * lr::kSegStride;
     for (int sc = 0; sc < 3; ++sc) {
@@ -286,6 +304,9 @@ int fit_orbits(double t0, double dt, int64_t n, const double* x_sc, const double
       double var = dt * (std::fabs(c[1]) + dt * (std::fabs(c[2]) + dt * std::fabs(c[3])));
       lmax = std::max(lmax, c[0] + var);
       lmin = std::min(lmin, c[0] - var);
+      rate = std::max(rate, std::fabs(c[1]) +
+                                dt * (2.0 * std::fabs(c[2]) + 3.0 * dt * std::fabs(c[3])));
+      if (k > 0) jump = std::max(jump, std::fabs(c[3] - c[3 - lr::kSegStride]));
     }
   }
   bounds = lr_orbits{};
@@ -296,6 +317,8 @@ int fit_orbits(double t0, double dt, int64_t n, const double* x_sc, const double
   bounds.L_min = lmin;
   bounds.L_max = lmax;
   bounds.R_max = rmax;
+  bounds.L_rate = rate;
+  bounds.L_jump = jump;
   return LR_OK;
 }
 
@@ -452,7 +475,7 @@ int lr_tdi_combine(const lr_orbits* orb, double t0_y, double dt, int64_t n_y, co
   a.n_out = n_out;
   a.channels = channels;
   a.out = out;
-  const lr::FirShape fs = lr::tdi_fir_shape(order, generation, orb->L_min, orb->L_max, dt,
+  const lr::FirShape fs = lr::tdi_fir_shape(order, generation, lr::light_times_of(*orb), dt,
                                             n_out, false);
   a.fir_lo = fs.lo;
   a.fir_k = fs.taps;
@@ -473,7 +496,7 @@ int lr_tdi_adjoint(const lr_orbits* orb, double t0_y, double dt, int64_t n_y, in
   if (overlap(g_y, 6 * n_y * sizeof(double), g_out, rows * n_out * sizeof(double)))
     return fail(LR_E_ARG, "g_y overlaps g_out");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const lr::FirShape fs = lr::tdi_fir_shape(order, generation, orb->L_min, orb->L_max, dt,
+  const lr::FirShape fs = lr::tdi_fir_shape(order, generation, lr::light_times_of(*orb), dt,
                                             n_y, true);
   hipError_t e;
   if (fs.taps == 0 || n_out == 0) {

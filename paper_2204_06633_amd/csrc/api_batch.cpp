@@ -100,7 +100,7 @@ FusedTile fused_tile(int tile, int halo, const lr::FirShape& fir, double L_max, 
 lr::FirShape batch_fir(int order, int generation, const lr_orbits& proj, const lr_orbits& tdi,
                        double dt) {
   if (!(proj.L_max <= kProjArm * tdi.L_max)) return {0, 0};
-  return lr::fused_fir_shape(order, generation, tdi.L_min, tdi.L_max, dt);
+  return lr::fused_fir_shape(order, generation, lr::light_times_of(tdi), dt);
 }
 
 size_t fir_table_bytes(const lr::FirShape& fir) {
@@ -137,7 +137,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
                                        "stencil needs %lld + %lld of %d link samples)",
                      dt, (long long)F, (long long)B, tile);
   // the tables' room depends on the TDI orbits alone: so does the workspace
-  P.fir = lr::fused_fir_shape(order, generation, tdi->L_min, tdi->L_max, dt);
+  P.fir = lr::fused_fir_shape(order, generation, lr::light_times_of(*tdi), dt);
   const FusedTile ft = fused_tile(tile, tile - P.T_out,
                                   batch_fir(order, generation, proj, *tdi, dt), tdi->L_max, dt);
   // and the work list is sized for the filters' tiles, which are the smaller
@@ -238,7 +238,7 @@ int make_plan(const lr_template* t, int64_t n, const lr_orbits* tdi, double dt, 
   // TDI adjoint: templates paired by duration (longer first), one work item
   // per (pair, tile) of the longer one: tiles of outputs that scatter, or of
   // link samples that gather where the filters serve
-  const bool gather = adjoint && lr::tdi_fir_shape(order, generation, tdi->L_min, tdi->L_max, dt,
+  const bool gather = adjoint && lr::tdi_fir_shape(order, generation, lr::light_times_of(*tdi), dt,
                                                    P.gy_doubles / 6, true).taps > 0;
   for (int64_t q = 0; q < n; q += 2) {
     const int64_t b0 = order_idx[q], b1 = q + 1 < n ? order_idx[q + 1] : -1;
@@ -364,7 +364,7 @@ int launch_forward(const lr_batch* b, const double* hp, const double* hc, const 
 // (which write it whole), else carry kernels (deterministic) where their rows
 // fit LDS, else atomic ones.
 hipError_t batch_tdi_adjoint(const lr_batch* b, lr::BatchAdjArgs a, hipStream_t s) {
-  const lr::FirShape fs = lr::tdi_fir_shape(b->order, b->generation, b->tdi.L_min, b->tdi.L_max,
+  const lr::FirShape fs = lr::tdi_fir_shape(b->order, b->generation, lr::light_times_of(b->tdi),
                                             b->dt, b->gy_doubles / 6, true);
   a.fir_lo = fs.lo;
   a.fir_k = fs.taps;

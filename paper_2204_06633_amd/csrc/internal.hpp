@@ -96,18 +96,30 @@ int set_error(int status, const char* fmt, ...);
 // per wave), or 0 if the rows do not fit LDS.
 int carry_row_capacity(int order, double spread, double dt, int rows, int ncarry, int extra);
 
+// What the choice of a TDI kernel reads of the light-time splines: bounds (s), of
+// the rate (s/s), the largest jump of a cubic coefficient (1/s^2) and the knots'
+// spacing (s).
+struct LightTimes {
+  double min, max, rate, jump, knot;
+};
+
 // Shape of the TDI filters (tdi_fir.hpp) for n samples: first tap relative to
 // the output and taps (even); taps = 0 where the delays are better interpolated
 // one by one.
 struct FirShape {
   int lo, taps;
 };
-FirShape tdi_fir_shape(int order, int gen, double L_min, double L_max, double dt, int64_t n,
-                       bool adjoint);
+FirShape tdi_fir_shape(int order, int gen, const LightTimes& L, double dt, int64_t n, bool adjoint);
 
 // The same for the fused batched forward (any group, so that results do not
 // depend on it).
-FirShape fused_fir_shape(int order, int gen, double L_min, double L_max, double dt);
+FirShape fused_fir_shape(int order, int gen, const LightTimes& L, double dt);
+
+// Light times of an orbit handle (lr_orbits).
+template <class Orbits>
+LightTimes light_times_of(const Orbits& o) {
+  return {o.L_min, o.L_max, o.L_rate, o.L_jump, o.dt};
+}
 
 // Polynomial projection kernels (farrow.hpp): lanes of a workgroup, runs of link
 // samples per workgroup.  farrow_rows: link samples per run of a workgroup of

@@ -14,7 +14,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 # LISARESP_LIB selects another build of the same library (tuning variants).
 LIB_PATH = os.environ.get("LISARESP_LIB") or os.path.join(_HERE, "_lisaresp.so")
 # LR_ABI_VERSION of include/lisaresp.h that the argument lists below follow
-ABI_VERSION = 5
+ABI_VERSION = 6
 
 LR_XYZ, LR_AET, LR_XYZ_AET = 0, 1, 2
 CHANNELS = {"XYZ": LR_XYZ, "AET": LR_AET, "XYZAET": LR_XYZ_AET}
@@ -33,7 +33,8 @@ LR_OK, LR_E_ARG, LR_E_RANGE, LR_E_UNSUPPORTED, LR_E_WORKSPACE, LR_E_HIP = range(
 class lr_orbits(ctypes.Structure):
     _fields_ = [("t0", ctypes.c_double), ("dt", ctypes.c_double), ("n", ctypes.c_int64),
                 ("coef", ctypes.c_void_p), ("L_min", ctypes.c_double),
-                ("L_max", ctypes.c_double), ("R_max", ctypes.c_double)]
+                ("L_max", ctypes.c_double), ("R_max", ctypes.c_double),
+                ("L_rate", ctypes.c_double), ("L_jump", ctypes.c_double)]
 
 
 _lib = None
