@@ -20,11 +20,15 @@
 // 256 lanes: four workgroups share a CU and hide each other's table phase
 // (1024 with 512 lanes halves the tables but measured 0.267 ms).
 //
-// The expansion is exact to rounding only while every delay keeps its integer
-// shift and stays smooth.  Each tile checks that at its nodes, its ends and (if
-// an orbit knot lies inside) 256 further times, and otherwise splits into
-// pieces that pass; a piece of one sample always does.  Light times that drift
-// as the constellation's do split about one tile in 500.
+// The expansion is exact to rounding where the light times are smooth, which the
+// host judges (fir_taps in api.cpp), and while every delay keeps its integer shift.
+// A tile in which one crosses an integer finds the outputs where that happens and
+// takes the pieces between them in turn, with the cubics of the whole tile: the
+// shift changes from piece to piece, the fraction just runs past 0 or 1.  With
+// Keplerian orbits few tiles of a year are such tiles (at most 2 in 100, where dt is
+// near a light time), of two or three pieces; a template of 1400 outputs with 25 to
+// 50 pieces in one tile (order 25, dt = 10 s) takes 190 to 300 us, and took up to
+// 1600 where the pieces were found by bisection (25 in one piece).
 #pragma once
 
 #include <float.h>
@@ -99,20 +103,19 @@ __device__ __forceinline__ double fir_point(int p) {
   return p == 2 || p == 3 || p == 4 ? -v : v;
 }
 
-// Largest change of a delay (samples) over an interval.  The cubic through
-// the nodes errs by (pi change / 2)^4 / 192 of the series at its worst, a
-// series at the Nyquist frequency: 1e-16 here.
-constexpr double kFirMaxChange = 2.4e-4;
+// Most outputs of an interval: a tile of the transpose is reached by kFwdTile + K - 1.
+constexpr int kFirMost = kFwdTile + 128;
 
 struct FirShared {
-  double L[6][6];    // light times at the six points
+  double L[6][6];                      // light times at the six points
+  unsigned long long brk[kFirMost / 64];   // outputs at which a delay's shift changes
 };
 
 // One term of one filter row at one node, held by lane 4 (12 term + row) +
 // node of the workgroup.
 struct FirLane {
   uint32_t term;
-  double shift, eps;   // a = -delay / dt = shift + eps at the lane's node
+  double a, shift;     // -delay / dt at the lane's node, its integer part on the piece
 };
 
 template <int GEN>
@@ -122,19 +125,30 @@ __device__ __forceinline__ uint32_t fir_lane_term() {
   return i < n ? fir_table<GEN>().term[i] : 0u;
 }
 
+// Delay of a term whose link light times are L, in seconds.
+__device__ __forceinline__ double fir_delay(uint32_t term, const double (&L)[6]) {
+  double d = 0.0;
+#pragma unroll
+  for (int l = 0; l < 6; ++l) d = fma((double)((term >> (4 * l)) & 15u), L[l], d);
+  return d;
+}
+
+// What rounding leaves open of a = -delay / dt: an excess over an integer of this
+// size is let through (the fraction then leaves [0, 1] by that much, where the two
+// stencils agree).
+__device__ __forceinline__ double fir_tolerance(double a) { return 1e-15 - 1e-15 * a; }
+
 // Light times of the interval (centre tc, half width hs seconds on the orbit
-// grid), the lane's term on it, and whether one cubic per tap serves the
-// interval: at the nodes and the ends every delay has one integer shift s
-// (s <= a <= s + 1) and changes little.  The extent of a is widened by a
-// quarter of itself (the delay between the points), and an excess of rounding
-// size is let through: eps then leaves [0, 1] by that much, where the two
-// stencils agree.  Barriers inside; W (n doubles) is cleared on the way.
+// grid), the lane's term on it, and whether every delay has one integer shift s
+// (s <= a <= s + 1): judged at the nodes and the ends, the extent of a widened by
+// a quarter of itself (the delay between the points).  Barriers inside; W (n
+// doubles) is cleared on the way.
 template <int GEN>
 __device__ __forceinline__ bool fir_regular(const OrbitView& orb, double tc, double hs,
                                             double inv_dt, FirShared& sh, FirLane& f, double* W,
                                             int n, int tid) {
-  // opaque copies: the term's decoding and the check's weights stay in here
-  // instead of being hoisted out of the callers' loops into scratch
+  // opaque copies: the term's decoding stays in here instead of being hoisted
+  // out of the callers' loops into scratch
   uint32_t term = f.term;
   asm volatile("" : "+v"(tid), "+v"(term));
   __syncthreads();
@@ -146,43 +160,71 @@ __device__ __forceinline__ bool fir_regular(const OrbitView& orb, double tc, dou
   }
   for (int e = tid; e < n; e += kBlock) W[e] = 0.0;
   __syncthreads();
-  double d = 0.0, e = 0.0;
-#pragma unroll
-  for (int l = 0; l < 6; ++l) {
-    const double c = (double)((term >> (4 * l)) & 15u);
-    d = fma(c, sh.L[tid & 3][l], d);
-    e = fma(c, sh.L[4 + (tid & 1)][l], e);
-  }
-  const double a = -d * inv_dt, b = -e * inv_dt;
+  const double a = -fir_delay(term, sh.L[tid & 3]) * inv_dt;
+  const double b = -fir_delay(term, sh.L[4 + (tid & 1)]) * inv_dt;
   double lo = fmin(a, b), hi = fmax(a, b);
   lo = fmin(lo, __shfl_xor(lo, 1));
   hi = fmax(hi, __shfl_xor(hi, 1));
   lo = fmin(lo, __shfl_xor(lo, 2));
   hi = fmax(hi, __shfl_xor(hi, 2));
-  const double change = hi - lo, tol = 1e-15 - 1e-15 * lo;
+  const double change = hi - lo, tol = fir_tolerance(lo);
+  f.a = a;
   f.shift = floor(lo - 0.25 * change + tol);
-  f.eps = a - f.shift;
-  bool ok = hi + 0.25 * change - tol <= f.shift + 1.0 && change <= kFirMaxChange;
-  // orbit knots inside: the splines' third derivative jumps there
-  double u;
-  if (orbit_segment(orb, tc - hs, u) != orbit_segment(orb, tc + hs, u)) {
-    const double x = -1.0 + (2.0 / (kBlock - 1)) * tid;
-    const double* seg = orbit_segment(orb, tc + hs * x, u);
-    // cubic through the nodes: even and odd part
-    constexpr double X = 1.0 / (kFirX0 * kFirX0 - kFirX1 * kFirX1);
-    const double e = (x * x - kFirX1 * kFirX1) * (0.5 * X), g = 0.5 - e;
-    const double eo = e * x * (1.0 / kFirX0), go = g * x * (1.0 / kFirX1);
-    constexpr double chain = GEN == 1 ? 3.0 : 7.0;
+  return __syncthreads_and(hi + 0.25 * change - tol <= f.shift + 1.0);
+}
+
+// The outputs among n (the first at time t0 on the orbit grid) at which some
+// delay's shift differs from the output before: every lane compares two
+// neighbours, the shifts folded into one number in base 3 (a delay changes by far
+// less than a sample over an interval, so a shift by one at most).
+template <int GEN>
+__device__ __forceinline__ void fir_breaks(const OrbitView& orb, double t0, double dt,
+                                           double inv_dt, int n, FirShared& sh, int tid) {
+  const GroupTable<GEN>& GT = group_table<GEN>();
+  auto fold = [&](int o) {
+    double u, L[6];
+    const double* seg = orbit_segment(orb, t0 + (double)o * dt, u);
 #pragma unroll
-    for (int l = 0; l < 6; ++l) {
-      const double v = (e + eo) * sh.L[0][l] + (g + go) * sh.L[1][l] + (g - go) * sh.L[2][l] +
-                       (e - eo) * sh.L[3][l];
-      // 1e-14 samples on the longest delay, above the rounding of the light times
-      ok &= chain * fabs(v - spline_at(seg, 9 + l, u)) * inv_dt <=
-            1e-14 + 2e-15 * chain * fabs(v) * inv_dt;
+    for (int l = 0; l < 6; ++l) L[l] = spline_at(seg, 9 + l, u);
+    unsigned long long h = 0;
+#pragma unroll 1
+    for (int g = 0; g < GT.n; ++g) {
+      const double a = -row_delay(GT.row[g], L) * inv_dt;
+      h = 3 * h + (unsigned long long)(long long)floor(a + fir_tolerance(a));
     }
+    return h;
+  };
+#pragma unroll 1
+  for (int o = tid; o < kFirMost; o += kBlock) {
+    const bool at = o > 0 && o < n && fold(o) != fold(o - 1);
+    const unsigned long long m = __ballot(at);
+    if ((tid & 63) == 0) sh.brk[o >> 6] = m;
   }
-  return __syncthreads_and(ok);
+  __syncthreads();
+}
+
+// First output after p at which a shift changes, or n.
+__device__ __forceinline__ int fir_next(const FirShared& sh, int p, int n) {
+  int w = (p + 1) >> 6;
+  unsigned long long m = w < kFirMost / 64 ? sh.brk[w] & (~0ull << ((p + 1) & 63)) : 0;
+  while (m == 0 && ++w < kFirMost / 64) m = sh.brk[w];
+  return m ? min(n, 64 * w + (int)__ffsll(m) - 1) : n;
+}
+
+// The lane's shift on the piece that starts at time t0.  Barriers inside; W is
+// cleared on the way.
+__device__ __forceinline__ void fir_shift(const OrbitView& orb, double t0, double inv_dt,
+                                          FirShared& sh, FirLane& f, double* W, int n, int tid) {
+  __syncthreads();
+  if (tid < 6) {
+    double u;
+    const double* seg = orbit_segment(orb, t0, u);
+    sh.L[4][tid] = spline_at(seg, 9 + tid, u);
+  }
+  for (int e = tid; e < n; e += kBlock) W[e] = 0.0;
+  __syncthreads();
+  const double a = -fir_delay(f.term, sh.L[4]) * inv_dt;
+  f.shift = floor(a + fir_tolerance(a));
 }
 
 // The filters of the interval as cubics in the interval's own time t in
@@ -197,7 +239,7 @@ __device__ __forceinline__ void fir_build(const FirLane& f, int lo, int K, doubl
   const bool direct = (f.term & 0xffffffu) == 0;
   const double sign = f.term & kFirMinusBit ? -1.0 : 1.0;
   double w[N];
-  lagrange_weights<N>(f.eps, w, sign);
+  lagrange_weights<N>(f.a - f.shift, w, sign);
   const int kb = min(max((int)f.shift - (N / 2 - 1) - lo, 0), K - N);
   double* row = W + (r >> 1) * 8 * K + (r & 1) * 4 + (tid & 3);
   // the terms of a row are added in turn
@@ -425,33 +467,12 @@ __host__ __device__ constexpr size_t fir_lds_doubles(int rows, int K) {
   return (size_t)rows * (kFwdTile + K) + 48 * K + 16;   // + 16: read ahead
 }
 
-// Interval [p0, p0 + len) of samples as centre (samples) and half width.
+// An interval of len outputs from output p0 on as centre (samples) and half width.
 struct FirPiece {
   double c, hw;
   __device__ __forceinline__ FirPiece(int64_t p0, int64_t len)
       : c((double)p0 + 0.5 * (double)(len - 1)), hw(0.5 * (double)(len - 1)) {}
-  __device__ __forceinline__ double inv() const { return hw > 0.0 ? 1.0 / hw : 0.0; }
+  __device__ __forceinline__ double inv() const { return 1.0 / hw; }
 };
-
-// Longest len <= most for which the samples [p0, p0 + len) (time t_off + p dt
-// on the orbit grid) are one interval; f holds the lane's term on it.
-template <int GEN>
-__device__ __forceinline__ int fir_extent(const OrbitView& orb, double t_off, double dt,
-                                          double inv_dt, int64_t p0, int most, FirShared& sh,
-                                          FirLane& f, double* W, int n, int tid) {
-  int good = 0, bad = most + 1, len = most;
-#pragma unroll 1
-  for (;;) {
-    const FirPiece P(p0, len);
-    if (fir_regular<GEN>(orb, t_off + P.c * dt, P.hw * dt, inv_dt, sh, f, W, n, tid) ||
-        len == 1)
-      good = len;                    // one sample is always an interval
-    else
-      bad = len;
-    if (bad - good > 1 && good < most) len = (good + bad) >> 1;
-    else if (len == good) return len;
-    else len = good;                 // f holds the failed length's term
-  }
-}
 
 }  // namespace lr

@@ -35,17 +35,24 @@ __global__ __launch_bounds__(kBlock, 4) void tdi_fir_kernel(TdiArgs a) {
   }
   bad = __syncthreads_or(bad);
 
+  // the whole tile's cubics, also where the series ends within it
+  const FirPiece P(0, kFwdTile);
+  const double t0 = a.t_off + (double)(a.out_start + i0) * a.dt;
+  const bool one =
+      fir_regular<GEN>(a.orb, t0 + P.c * a.dt, P.hw * a.dt, a.inv_dt, sh, f, W, 48 * K, tid);
+  if (!one) fir_breaks<GEN>(a.orb, t0, a.dt, a.inv_dt, cnt, sh, tid);
 #pragma unroll 1
   for (int p0 = 0; p0 < cnt;) {
     // an opaque lane index per piece: what derives from it is computed here
     // and not hoisted out of the loop into scratch
     int t = tid;
     asm volatile("" : "+v"(t));
-    const int64_t q0 = a.out_start + i0 + p0;                // y-index
-    const int len =
-        fir_extent<GEN>(a.orb, a.t_off, a.dt, a.inv_dt, q0, cnt - p0, sh, f, W, 48 * K, t);
+    int len = cnt;
+    if (!one) {
+      len = fir_next(sh, p0, cnt) - p0;
+      fir_shift(a.orb, t0 + (double)p0 * a.dt, a.inv_dt, sh, f, W, 48 * K, t);
+    }
     fir_build<N, GEN, false>(f, lo, K, 0.0, W, t);
-    const FirPiece P(p0, len);
     double v[2][3];
     if (!bad) {
       double S[3][2][4];
@@ -146,12 +153,23 @@ __device__ __forceinline__ void tdi_fir_adjoint_tile(const TdiAdjArgs (&a)[M],
         for (int l = 0; l < 6; ++l) a[m].g_y[(int64_t)l * a[m].n_y + s0 + i] = 0.0;
     return;
   }
+  // one interval for all outputs that could reach the tile
+  const FirPiece P(ob, kFwdTile + K - 1);
+  const double dt = a[0].dt, inv_dt = a[0].inv_dt;
+  const double t0 = a[0].t_off + (double)a[0].out_start * dt;        // time of output 0
+  const int n = (int)(o2 - o1);
+  const bool one =
+      fir_regular<GEN>(a[0].orb, t0 + P.c * dt, P.hw * dt, inv_dt, sh, f, W, 48 * K, tid);
+  if (!one) fir_breaks<GEN>(a[0].orb, t0 + (double)o1 * dt, dt, inv_dt, n, sh, tid);
 #pragma unroll 1
   for (int64_t p0 = o1; p0 < o2;) {
     int t = tid;
     asm volatile("" : "+v"(t));
-    const int len = fir_extent<GEN>(a[0].orb, a[0].t_off, a[0].dt, a[0].inv_dt,
-                                    a[0].out_start + p0, (int)(o2 - p0), sh, f, W, 48 * K, t);
+    int len = n;
+    if (!one) {
+      len = fir_next(sh, (int)(p0 - o1), n) - (int)(p0 - o1);
+      fir_shift(a[0].orb, t0 + (double)p0 * dt, inv_dt, sh, f, W, 48 * K, t);
+    }
     // the piece's outputs, zero outside it
     bool bad = false;
 #pragma unroll
@@ -169,7 +187,6 @@ __device__ __forceinline__ void tdi_fir_adjoint_tile(const TdiAdjArgs (&a)[M],
         }
       }
     }
-    const FirPiece P(p0, len);
     fir_build<N, GEN, true>(f, lo, K, P.inv(), W, t);
     bad = __syncthreads_or(bad);
     const double x0 = ((double)(s0 + 2 * t - a[0].out_start) - P.c) * P.inv();
@@ -265,8 +282,8 @@ hipError_t launch_batch_tdi_fir_adjoint(const BatchAdjArgs& a, int64_t n_items, 
 }
 
 // Tables of the batched forward: one workgroup per interval of kFirInterval
-// outputs, built in LDS and stored; a flag where one cubic per tap does not
-// serve the interval.  The workgroups after them do what precedes a fused
+// outputs, built in LDS and stored; a flag where a delay crosses an integer within
+// the interval.  The workgroups after them do what precedes a fused
 // forward anyway (run_forward_prep): the work counter and the sky angles'
 // sines and cosines.
 template <int N, int GEN>

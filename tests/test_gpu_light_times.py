@@ -114,3 +114,32 @@ def test_batched_transpose(torch_cuda, kind, spacing, bad):
         assert np.array_equal(ok, np.isfinite(mine)), (k, n)
         assert ok.all() == (bad is None or n != 1400)
         cases.check(mine[ok], ref[ok], 1e-10, "template %d" % k)
+
+
+@pytest.mark.parametrize("apart", [1.3, 40.0])
+def test_crossings_cost_little(torch_cuda, apart):
+    """A short template in which delays cross integers takes a few times as long as
+    one in which none does, at most: it is one tile's work in some more pieces."""
+    from paper_2204_06633_amd import native
+    torch = torch_cuda
+    n_out, t0, start = 1400, T0 + 1000.0, 60
+    s = inputs.make_orbit_samples("keplerian", T0, T0 + 3e4)
+    times = []
+    for sample in (s, _light_times(s, "crossing%g" % apart, t0 + DT * (start + 200))):
+        orb = native.Orbits.from_samples(sample)
+        n_y = start + n_out + orb.tdi_padding(ORDER, 2, DT)[1] + 4
+        y = torch.zeros((6, n_y), dtype=torch.float64, device="cuda")
+        out = torch.zeros((3, n_out), dtype=torch.float64, device="cuda")
+        best = [1e9, 1e9]
+        for _ in range(12):
+            for i, call in enumerate((
+                    lambda: native.tdi_combine(orb, t0, DT, y, 2, ORDER, "XYZ", start, n_out, out=out),
+                    lambda: native.tdi_adjoint(orb, t0, DT, n_y, 2, ORDER, "XYZ", start, out, g_y=y))):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                call()
+                b.record()
+                b.synchronize()
+                best[i] = min(best[i], a.elapsed_time(b))
+        times.append(best)
+    assert times[1][0] < 12.0 * times[0][0] and times[1][1] < 12.0 * times[0][1], times
