@@ -472,7 +472,7 @@ struct FirPiece {
   double c, hw;
   __device__ __forceinline__ FirPiece(int64_t p0, int64_t len)
       : c((double)p0 + 0.5 * (double)(len - 1)), hw(0.5 * (double)(len - 1)) {}
-  __device__ __forceinline__ double inv() const { return 1.0 / hw; }
+  __device__ __forceinline__ double inv() const { return hw > 0.0 ? 1.0 / hw : 0.0; }
 };
 
 }  // namespace lr

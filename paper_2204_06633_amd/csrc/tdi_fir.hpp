@@ -35,8 +35,7 @@ __global__ __launch_bounds__(kBlock, 4) void tdi_fir_kernel(TdiArgs a) {
   }
   bad = __syncthreads_or(bad);
 
-  // the whole tile's cubics, also where the series ends within it
-  const FirPiece P(0, kFwdTile);
+  const FirPiece P(0, cnt);
   const double t0 = a.t_off + (double)(a.out_start + i0) * a.dt;
   const bool one =
       fir_regular<GEN>(a.orb, t0 + P.c * a.dt, P.hw * a.dt, a.inv_dt, sh, f, W, 48 * K, tid);
@@ -153,11 +152,10 @@ __device__ __forceinline__ void tdi_fir_adjoint_tile(const TdiAdjArgs (&a)[M],
         for (int l = 0; l < 6; ++l) a[m].g_y[(int64_t)l * a[m].n_y + s0 + i] = 0.0;
     return;
   }
-  // one interval for all outputs that could reach the tile
-  const FirPiece P(ob, kFwdTile + K - 1);
+  const int n = (int)(o2 - o1);
+  const FirPiece P(o1, n);
   const double dt = a[0].dt, inv_dt = a[0].inv_dt;
   const double t0 = a[0].t_off + (double)a[0].out_start * dt;        // time of output 0
-  const int n = (int)(o2 - o1);
   const bool one =
       fir_regular<GEN>(a[0].orb, t0 + P.c * dt, P.hw * dt, inv_dt, sh, f, W, 48 * K, tid);
   if (!one) fir_breaks<GEN>(a[0].orb, t0 + (double)o1 * dt, dt, inv_dt, n, sh, tid);
