@@ -90,6 +90,44 @@ __device__ __forceinline__ void fused_tdi_fir(const double* ylds, const double2*
   });
 }
 
+// The same with the same bits where link samples of the segment are not finite: a tap
+// that is empty must not spread a NaN or an infinity past the stencils, and is passed
+// over.  tab: the interval's table.
+template <int GEN, int M, int YR>
+__device__ __forceinline__ void fused_tdi_careful(const double* ylds, const double* tab, int K,
+                                                  int j0, const double (&t)[3],
+                                                  const double (&u)[3], double (&acc)[M][2][3]) {
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) acc[m][0][c] = acc[m][1][c] = 0.0;
+#pragma unroll 1
+  for (int l = 0; l < 6; ++l)
+#pragma unroll 1
+    for (int k = 0; k < K; ++k)
+#pragma unroll 1
+      for (int i = 0; i < 2; ++i) {
+        const int ch = fir_table<GEN>().chan[2 * l + i];
+        const double* w = tab + 32 * (l * fir_quads(K) + (k >> 2)) + ((k >> 1) & 1) +
+                          16 * (k & 1) + 8 * i;
+        const double c0 = w[0], c1 = w[2], c2 = w[4], c3 = w[6];
+        if (c0 == 0.0 && c1 == 0.0 && c2 == 0.0 && c3 == 0.0) continue;
+        const double p = fma(c3, t[2], fma(c2, t[1], fma(c1, t[0], c0)));
+        const double r = fma(c3, u[2], fma(c2, u[1], fma(c1, u[0], c0)));
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+          const double* y = ylds + (m * 6 + l) * YR;
+          const double a = y[par<YR>(j0 + k)], b = y[par<YR>(j0 + k + 1)];
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            if (c == ch) {
+              acc[m][0][c] = fma(p, a, acc[m][0][c]);
+              acc[m][1][c] = fma(r, b, acc[m][1][c]);
+            }
+        }
+      }
+}
+
 // WAVE: h+ / hx synthesised from each template's parameter row (Sec. III)
 // instead of read from the caller's arrays.  A compile-time choice: with the
 // waveform code in the same kernel the array path's registers spill.
@@ -196,12 +234,9 @@ void fused_forward_kernel(BatchFwdArgs a) {
       const bool out_a = oa >= 0 && oa < cnt;
       const int ob = max(0, min(oa, cnt - 2));        // idle lanes mirror the ends
       double acc[M][2][3];
-      // The filters' empty taps would spread a NaN or an infinity past the
-      // stencils: such segments interpolate the delays one by one, like the
-      // intervals that no filter serves.
       bad = __syncthreads_or(bad);
-      bool split = bad;
-      if (!split) {
+      bool split = false;
+      {
         // outputs past the longest template of the batch have no interval, and
         // are not stored
         const int64_t o = o0 + ob;
@@ -217,8 +252,12 @@ void fused_forward_kernel(BatchFwdArgs a) {
         ta[2] = ta[1] * ta[0];
         tb[2] = tb[1] * tb[0];
         const double2* W = reinterpret_cast<const double2*>(a.fir) +
-                           (int64_t)q * 96 * fir_quads(a.fir_k) + (tid & 15);
-        fused_tdi_fir<GEN, M, YR>(ylds, W, a.fir_k, a.F + a.fir_lo + ro + ob, ta, tb, acc);
+                           (int64_t)q * 96 * fir_quads(a.fir_k);
+        const int j0 = a.F + a.fir_lo + ro + ob;
+        if (!bad)
+          fused_tdi_fir<GEN, M, YR>(ylds, W + (tid & 15), a.fir_k, j0, ta, tb, acc);
+        else
+          fused_tdi_careful<GEN, M, YR>(ylds, &W->x, a.fir_k, j0, ta, tb, acc);
         for (int i = q0; i <= q1; ++i) split |= a.fir_split[i] != 0;
       }
       if (split) {                                    // uniform
@@ -226,8 +265,7 @@ void fused_forward_kernel(BatchFwdArgs a) {
         light_times(a.orb_t, a.t_off_t + (double)(o0 + ob) * a.dt, La);
         light_times(a.orb_t, a.t_off_t + (double)(o0 + ob + 1) * a.dt, Lb);
         fused_tdi<N, GEN, M, YR, false>(a, ylds, La, Lb, a.F + ro + ob, live, one);
-        const bool mine =
-            bad || a.fir_split[min((o0 + ob) / kFirInterval, a.n_fir - 1)] != 0;
+        const bool mine = a.fir_split[min((o0 + ob) / kFirInterval, a.n_fir - 1)] != 0;
 #pragma unroll
         for (int k = 0; k < M; ++k)
 #pragma unroll

@@ -240,6 +240,10 @@ __device__ __forceinline__ void fir_build(const FirLane& f, int lo, int K, doubl
   const double sign = f.term & kFirMinusBit ? -1.0 : 1.0;
   double w[N];
   lagrange_weights<N>(f.a - f.shift, w, sign);
+  // a weight that is exactly zero (a delay of whole samples) leaves its tap in the
+  // stencil, though a trace only: a NaN there still counts
+#pragma unroll
+  for (int m = 0; m < N; ++m) w[m] = w[m] == 0.0 ? 1e-300 : w[m];
   const int kb = min(max((int)f.shift - (N / 2 - 1) - lo, 0), K - N);
   double* row = W + (r >> 1) * 8 * K + (r & 1) * 4 + (tid & 3);
   // the terms of a row are added in turn
