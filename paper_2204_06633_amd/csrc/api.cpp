@@ -47,12 +47,7 @@ int carry_row_capacity(int order, double spread, double dt, int rows, int ncarry
 
 // The filters need positive light times (every delayed stencil then ends
 // before tap o + N / 2) and rows that fit LDS.  Elsewhere the faster kernel is
-// taken, from the times (us) of both on one MI355X: 3,155,760 samples where
-// the device is full, 32,768 (latency) below 2^19; filters linear in the taps,
-// one-by-one kernels in N.  At order 25 and dt = 10 s (32 taps): generation 2
-// forward 232 against 535, adjoint 260 against 842; generation 1 forward 202
-// against 254; 32,768 samples of generation 2 20.8 against 40.8.  At dt = 2 s
-// the taps outgrow N and low orders and generation 1 stay with the streams.
+// taken (tdi_fir_shape).
 //
 // They also need light times that one cubic per tap follows over a tile and what
 // reaches it (512 outputs and the taps): a delay that changes by at most 2.4e-4 of
@@ -80,13 +75,29 @@ static FirShape fir_taps(int order, int gen, const LightTimes& L, double dt, dou
 FirShape tdi_fir_shape(int order, int gen, const LightTimes& L, double dt, int64_t n,
                        bool adjoint) {
   const FirShape f = fir_taps(order, gen, L, dt, 40.0);
-  // {intercept, slope}: filters, one by one in generation 1 and 2
-  constexpr double fwd[2][6] = {{8.5, 0.38, 12.0, 0.31, 20.0, 0.68},
-                                {33.0, 6.2, 66.0, 7.4, 85.0, 17.6}};
-  constexpr double adj[2][6] = {{9.0, 0.45, 22.0, 0.5, 30.0, 1.1},
-                                {47.0, 6.65, 170.0, 11.9, 165.0, 26.0}};
-  const double* t = (adjoint ? adj : fwd)[n > ((int64_t)1 << 19)];
-  if (t[0] + t[1] * f.taps > t[2 * gen] + t[2 * gen + 1] * (order + 1)) return {0, 0};
+  // Times of both kernels (us) on one MI355X as lines, filters in the taps and one by
+  // one in N: {intercept, slope} of generation 1 and 2 with filters, then one by
+  // one, at 32,768 outputs (latency) and at 1.6 million, and between and beyond along
+  // the outputs.  At order 25 and dt = 10 s: generation 2 forward 122 against 277,
+  // transpose 137 against 452; generation 1 forward 117 against 136; 200,000 outputs of
+  // generation 2 29 against 54.  At dt = 2 s and below the taps outgrow N, and low
+  // orders and generation 1 stay with the streams: order 7, dt = 5 s, generation 1 75
+  // against 73, order 1, dt = 2.5 s, 200,000 outputs of generation 2 24 against 21.
+  struct Line {
+    double a, b;
+  };
+  constexpr Line lines[2][2][4] = {
+      {{{8.5, 0.38}, {8.5, 0.38}, {12.0, 0.31}, {20.0, 0.68}},
+       {{32.0, 3.05}, {26.0, 3.05}, {42.0, 3.7}, {57.0, 8.6}}},
+      {{{9.0, 0.45}, {9.0, 0.45}, {22.0, 0.5}, {30.0, 1.1}},
+       {{37.0, 3.3}, {37.0, 3.3}, {90.0, 5.5}, {115.0, 10.5}}}};
+  const double x = std::max(0.0, (double)(n - 32768) / (1600000.0 - 32768.0));
+  auto time = [&](int k, double v) {
+    const Line &few = lines[adjoint][0][k], &many = lines[adjoint][1][k];
+    const double t = few.a + few.b * v;
+    return t + x * (many.a + many.b * v - t);
+  };
+  if (time(gen - 1, f.taps) > time(gen + 1, order + 1)) return {0, 0};
   return f;
 }
 

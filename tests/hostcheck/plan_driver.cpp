@@ -1,8 +1,10 @@
-// Prints the work plan of a fused batched forward: every line of standard input
-// is one batch (order, generation, dt, longest light times of the projection and
-// of the TDI orbits, group, tile, segment, number of templates, their outputs),
-// and is answered with the plan as the kernel launch receives it, one JSON object
-// per line.  The launchers are stubs, and the copies to the device go to host memory.
+// Prints what kernel launches receive, one JSON object per line of standard input.
+// "batch": the work plan of a fused batched forward (order, generation, dt, longest
+// light times of the projection and of the TDI orbits, group, tile, segment, number
+// of templates, their outputs).  "tdi": the taps of the filters of a TDI call and of
+// its transpose, 0 for the kernels of single delays (order, generation, dt, longest
+// light time, outputs).  The launchers are stubs, and the copies to the device go
+// to host memory.
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -10,6 +12,7 @@
 
 #include "../../include/lisaresp.h"
 #include "../../paper_2204_06633_amd/csrc/batch_types.hpp"
+#include "../../paper_2204_06633_amd/csrc/internal.hpp"
 
 extern "C" {
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
@@ -30,13 +33,47 @@ hipError_t run_fused_forward(int, int, int, int, bool, const BatchFwdArgs& a, in
   std::printf("], ");
   return hipSuccess;
 }
+hipError_t run_tdi(int, int, const TdiArgs& a, hipStream_t) {
+  std::printf("{\"forward\": %d, ", a.fir_k);
+  return hipSuccess;
+}
+hipError_t run_tdi_adjoint(int, int, const TdiAdjArgs& a, hipStream_t) {
+  std::printf("\"transpose\": %d}\n", a.fir_k);
+  return hipSuccess;
+}
 }  // namespace lr
+
+static bool tdi() {
+  int order, gen;
+  double dt, arm, any[1];
+  long long n;
+  if (std::scanf("%d %d %lf %lf %lld", &order, &gen, &dt, &arm, &n) != 5) return false;
+  lr_orbits o{};
+  o.dt = 1e7;
+  o.n = 100;
+  o.coef = any;
+  o.L_max = arm;
+  o.L_min = 0.98 * arm;
+  o.R_max = 1.6e11;
+  int64_t f, b;
+  if (lr_tdi_padding(&o, order, gen, dt, &f, &b)) return false;
+  const auto y = reinterpret_cast<double*>(uintptr_t{1} << 40), g = y + (int64_t{1} << 40);
+  return !lr_tdi_combine(&o, 1e6, dt, f + n + b, y, gen, order, LR_AET, f, n, g, nullptr) &&
+         !lr_tdi_adjoint(&o, 1e6, dt, f + n + b, gen, order, LR_AET, f, n, g, y, nullptr);
+}
 
 int main() {
   int order, gen, group, tile, segment, n;
   double dt, arm_p, arm_t;
-  while (std::scanf("%d %d %lf %lf %lf %d %d %d %d", &order, &gen, &dt, &arm_p, &arm_t, &group,
-                    &tile, &segment, &n) == 9) {
+  char kind[16];
+  while (std::scanf("%15s", kind) == 1) {
+    if (std::strcmp(kind, "tdi") == 0) {
+      if (!tdi()) return 1;
+      continue;
+    }
+    if (std::scanf("%d %d %lf %lf %lf %d %d %d %d", &order, &gen, &dt, &arm_p, &arm_t, &group,
+                   &tile, &segment, &n) != 9)
+      return 1;
     double coef[4] = {0.0};
     lr_orbits p{}, t{};
     p.dt = t.dt = 1e7;

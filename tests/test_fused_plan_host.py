@@ -48,7 +48,9 @@ def plans(tmp_path_factory):
           "-I" + os.path.join(ROOT, "include")]
     objs = []
     for src, extra in ((os.path.join(HC, "plan_driver.cpp"), []),
-                       (os.path.join(HC, "launch_stubs.cpp"), ["-Drun_fused_forward=unused_stub"]),
+                       (os.path.join(HC, "launch_stubs.cpp"),
+                        ["-D%s=unused_%s" % (f, f)
+                         for f in ("run_fused_forward", "run_tdi", "run_tdi_adjoint")]),
                        (os.path.join(csrc, "api.cpp"), []), (os.path.join(csrc, "api_batch.cpp"), [])):
         objs.append(str(tmp / (os.path.basename(src) + ".o")))
         subprocess.check_call(cc + extra + ["-c", src, "-o", objs[-1]], stderr=subprocess.DEVNULL)
@@ -56,8 +58,10 @@ def plans(tmp_path_factory):
     subprocess.check_call(cc + objs + ["-o", exe] + build.link_flags(), stderr=subprocess.DEVNULL)
 
     def run(cases):
-        """cases: (order, gen, dt, projection arm, TDI arm, group, tile, segment, sizes)."""
-        text = "".join("%d %d %r %r %r %d %d %d %d %s\n"
+        """cases: (order, gen, dt, projection arm, TDI arm, group, tile, segment, sizes)
+        of a batch, or (order, gen, dt, arm, outputs) of a TDI call."""
+        text = "".join("tdi %d %d %r %r %d\n" % c if len(c) == 5 else
+                       "batch %d %d %r %r %r %d %d %d %d %s\n"
                        % (*c[:8], len(c[8]), " ".join(map(str, c[8]))) for c in cases)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=300)
         assert out.returncode == 0, out.stderr
@@ -179,3 +183,25 @@ def test_longer_projection_arms_leave_the_filters(plans):
     for arm, filters in ((ARM, True), (1.2 * ARM, True), (1.3 * ARM, False), (40.0, False)):
         p, = plans([(25, 2, 2.0, arm, ARM, 2, 512, 0, SIZES)])
         assert (p["fir_k"] > 0) == filters, arm
+
+
+# (order, generation, dt, outputs, filters forward, transpose): us one by one and with
+# filters beside each line
+TDI_ROUTES = [(1, 2, 2.5, 200000, False, True),        # 21.1, 23.8; 36.7, 27.3
+              (3, 1, 5.0, 1600000, False, True),       # 56.8, 60.8; 126, 74
+              (7, 1, 1.0, 200000, False, False),       # 18.7, -; 30.8, 34.0
+              (7, 1, 10.0, 1600000, True, True),       # 72.7, 62.1; 125.6, 74.1
+              (7, 1, 1.0, 1600000, False, False),      # 72.9, -; 128, 127 (filters by count 149)
+              (25, 1, 1.0, 1600000, False, True),      # 136, -; 264, 205
+              (1, 2, 5.0, 1600000, True, True),        # 72.3, 66.6; 136, 76.7
+              (7, 2, 2.5, 1600000, True, True),        # 124.8, 124.3; 185.7, 130.6
+              (25, 2, 1.55, 1600000, True, True),      # 302, 244; 480, 262
+              (25, 2, 10.0, 8640, True, True),         # 25, 17; 76, 24
+              (1, 1, 10.0, 8640, True, True),          # 12, 10; 27, 15
+              (25, 2, 1.0, 1600000, False, False)]     # too many taps for LDS
+
+
+@pytest.mark.parametrize("order,gen,dt,n,forward,transpose", TDI_ROUTES)
+def test_tdi_filters_only_where_they_are_faster(plans, order, gen, dt, n, forward, transpose):
+    p, = plans([(order, gen, dt, ARM, n)])
+    assert (p["forward"] > 0, p["transpose"] > 0) == (forward, transpose)
