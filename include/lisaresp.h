@@ -89,6 +89,8 @@ typedef struct {
     double L_jump;       /* largest jump of a light-time spline's cubic coefficient
                             at a knot (s/s^3): with L_rate, how smooth the light times
                             are, which decides how the TDI calls interpolate */
+    double D_max, V_max; /* rigorous bounds of the distance between two spacecraft (m)
+                            and of |dx/dt| (m/s) over the position splines */
 } lr_orbits;
 
 /* Bytes of device storage lr_orbits_init needs for n coarse samples. */
@@ -166,12 +168,14 @@ int lr_tdi_combine(const lr_orbits *orb, double t0_y, double dt, int64_t n_y, co
  * Adjoints.  Not in the paper; they are the exact transposes of the linear
  * maps above (derived from Sec. IV.B-IV.C and the interpolation of
  * Sec. IV.E), so that a likelihood gradient can flow from the TDI channels
- * back to h+, hx and the sky angles.  The TDI transpose gathers through
- * filters; the projection's sums a tile's gradients in a fixed order, and every
- * output element receives at most two tile sums (added onto zero, which
- * commutes): results are bitwise reproducible.  Exception: when dt is so small against the light times that
- * a wave's footprint does not fit LDS (about dt < L/50), LDS and global
- * atomics take over and results are reproducible to rounding only.
+ * back to h+, hx and the sky angles.  Results are bitwise reproducible: the TDI
+ * transpose gathers (or sums in a fixed order), the projection's sums a tile's
+ * gradients in a fixed order, and an output element receives at most two tile
+ * sums (added onto zero, which commutes).  To rounding only are they
+ * reproducible where atomics meet more often at an element: when dt is so small
+ * against the light times that a wave's footprint does not fit LDS (about dt <
+ * L/50), and in the projection's adjoint over orbits whose positions lie further
+ * apart than 2.01 light times or pass through many samples within one tile.
  * ---------------------------------------------------------------------- */
 
 /* g_y = T^T g_out: transpose of lr_tdi_combine with the same arguments.
@@ -316,10 +320,8 @@ int lr_response_gb(const lr_batch *b, const double *params, double *out, void *s
  * g_out laid out like out; g_hp, g_hc like hp, hc over [0, h_extent),
  * overwritten; g_sky device [n][2] (d/d lam, d/d beta) or NULL (then hp, hc
  * may be NULL too).  Graph-capturable; calls sharing one lr_batch must not
- * overlap.  Results are bitwise reproducible unless dt is so small (below
- * about a fiftieth of the light time) that the scatter footprints do not fit
- * LDS; then atomics reorder the sums and results are reproducible to
- * rounding.
+ * overlap.  Results are bitwise reproducible, with the exceptions of the
+ * single-template adjoints (very small dt, extreme orbits).
  * Errors: LR_E_WORKSPACE (batch prepared without adjoint), LR_E_ARG,
  * LR_E_HIP. */
 int lr_response_adjoint(const lr_batch *b, const double *hp, const double *hc,

@@ -300,23 +300,34 @@ int fit_orbits(double t0, double dt, int64_t n, const double* x_sc, const double
     fit_not_a_knot(ltt + l, 6, n, dt, coef.data() + 4 * (9 + l), lr::kSegStride);
 
   double rmax = 0.0, lmax = -INFINITY, lmin = INFINITY, rate = 0.0, jump = 0.0;
+  double apart = 0.0, speed = 0.0;
+  auto slope = [dt](const double* c) {
+    return std::fabs(c[1]) + dt * (2.0 * std::fabs(c[2]) + 3.0 * dt * std::fabs(c[3]));
+  };
   for (int64_t k = 0; k < nseg; ++k) {
     const double* seg = coef.data() + k * lr::kSegStride;
     for (int sc = 0; sc < 3; ++sc) {
-      double r2 = 0.0;
+      double r2 = 0.0, v2 = 0.0, d2 = 0.0;
       for (int c = 0; c < 3; ++c) {
-        double b = seg_abs_bound(seg + 4 * (3 * sc + c), dt);
+        const double* a = seg + 4 * (3 * sc + c);
+        double b = seg_abs_bound(a, dt);
         r2 += b * b;
+        v2 += slope(a) * slope(a);
+        double d[4];
+        for (int k = 0; k < 4; ++k) d[k] = a[k] - seg[4 * (3 * ((sc + 1) % 3) + c) + k];
+        b = seg_abs_bound(d, dt);
+        d2 += b * b;
       }
       rmax = std::max(rmax, std::sqrt(r2));
+      speed = std::max(speed, std::sqrt(v2));
+      apart = std::max(apart, std::sqrt(d2));
     }
     for (int l = 0; l < 6; ++l) {
       const double* c = seg + 4 * (9 + l);
       double var = dt * (std::fabs(c[1]) + dt * (std::fabs(c[2]) + dt * std::fabs(c[3])));
       lmax = std::max(lmax, c[0] + var);
       lmin = std::min(lmin, c[0] - var);
-      rate = std::max(rate, std::fabs(c[1]) +
-                                dt * (2.0 * std::fabs(c[2]) + 3.0 * dt * std::fabs(c[3])));
+      rate = std::max(rate, slope(c));
       if (k > 0) jump = std::max(jump, std::fabs(c[3] - c[3 - lr::kSegStride]));
     }
   }
@@ -330,6 +341,8 @@ int fit_orbits(double t0, double dt, int64_t n, const double* x_sc, const double
   bounds.R_max = rmax;
   bounds.L_rate = rate;
   bounds.L_jump = jump;
+  bounds.D_max = apart;
+  bounds.V_max = speed;
   return LR_OK;
 }
 

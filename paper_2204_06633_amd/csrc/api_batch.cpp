@@ -24,7 +24,7 @@ constexpr int64_t kAdjTile = 256;     // samples per adjoint work item (atomic k
 constexpr int64_t kCarryTile = 512;   // samples per work item of the carry adjoint kernels
 constexpr int64_t kFirOutputs = 512;  // outputs per TDI filter table
 constexpr int64_t kLikeChunk = 8192;  // elements per likelihood work item
-constexpr double kProjArm = 1.25;     // longest projection arms a fused run holds, in TDI arms
+constexpr double kProjArm = 1.25;     // arms a fused run holds, in longest TDI arms
 
 enum Region {
   R_TPL, R_ITEMS, R_COUNTER, R_ADJ_TPL, R_TDI_ITEMS, R_PROJ_ITEMS, R_SKY_PART, R_SKY_SPAN,
@@ -95,11 +95,16 @@ FusedTile fused_tile(int tile, int halo, const lr::FirShape& fir, double L_max, 
   return f;
 }
 
-// The filters of a batch with these orbits: none where the projection's arms
-// are so much longer than the TDI's that its runs would not hold the positions.
+// The filters of a batch with these orbits: none where the projection's positions may
+// lie further apart in a run than fused_tile leaves room for (they spread by the
+// spacecraft's distance, a light time and what they move).  Runs that do not fit
+// read single stencils, which round differently, and which runs those are would
+// depend on how the batch is cut.
 lr::FirShape batch_fir(int order, int generation, const lr_orbits& proj, const lr_orbits& tdi,
                        double dt) {
-  if (!(proj.L_max <= kProjArm * tdi.L_max)) return {0, 0};
+  const double spread = (proj.D_max / lr::kC + proj.L_max) / dt + proj.V_max / lr::kC * 512.0;
+  const double room = std::ceil(2.01 * kProjArm * tdi.L_max / dt) + 2.0;
+  if (!(std::ceil(spread) <= room)) return {0, 0};
   return lr::fused_fir_shape(order, generation, lr::light_times_of(tdi), dt);
 }
 

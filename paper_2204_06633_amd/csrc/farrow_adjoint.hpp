@@ -14,7 +14,9 @@
 //      into the gradients of the N samples around J, summed in the wave's own
 //      LDS row (LDS adds of one wave stay in order), then over the waves, and
 //      added to the zero-filled gradients.  An element receives at most two
-//      additions there, so results are bitwise reproducible.
+//      additions there, so results are bitwise reproducible -- but for positions
+//      further apart than `rows` allows for, which are served one after the other,
+//      and for ones that move so fast that runs are halved: then more meet.
 //   C. lane = link sample: sky gradient from the values and derivatives.
 //
 // Bound by FP64 issue at two waves per SIMD (registers: 64 coefficients and

@@ -34,7 +34,8 @@ class lr_orbits(ctypes.Structure):
     _fields_ = [("t0", ctypes.c_double), ("dt", ctypes.c_double), ("n", ctypes.c_int64),
                 ("coef", ctypes.c_void_p), ("L_min", ctypes.c_double),
                 ("L_max", ctypes.c_double), ("R_max", ctypes.c_double),
-                ("L_rate", ctypes.c_double), ("L_jump", ctypes.c_double)]
+                ("L_rate", ctypes.c_double), ("L_jump", ctypes.c_double),
+                ("D_max", ctypes.c_double), ("V_max", ctypes.c_double)]
 
 
 _lib = None

@@ -84,6 +84,8 @@ int main() {
     p.L_min = 0.98 * arm_p;
     t.L_min = 0.98 * arm_t;
     p.R_max = t.R_max = 1.6e11;
+    p.D_max = 299792458.0 * arm_p;
+    p.V_max = 3e4;
     int64_t fp, bp, ft, bt;
     if (lr_projection_padding(&p, order, dt, &fp, &bp) ||
         lr_tdi_padding(&t, order, gen, dt, &ft, &bt))

@@ -180,7 +180,7 @@ def test_filters_only_where_they_are_faster(plans, order, gen, dt, filters):
 def test_longer_projection_arms_leave_the_filters(plans):
     """Runs are sized by the TDI's light times: projection orbits that spread the
     positions further take the kernel whose window holds them."""
-    for arm, filters in ((ARM, True), (1.2 * ARM, True), (1.3 * ARM, False), (40.0, False)):
+    for arm, filters in ((ARM, True), (1.2 * ARM, True), (1.7 * ARM, False), (40.0, False)):
         p, = plans([(25, 2, 2.0, arm, ARM, 2, 512, 0, SIZES)])
         assert (p["fir_k"] > 0) == filters, arm
 

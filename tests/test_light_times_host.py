@@ -40,6 +40,20 @@ def test_rate_and_jump_bound_the_splines(kind, spacing):
     assert abs(b.L_jump - jump) <= 64.0 * 2e-15 / s.dt ** 3
 
 
+@pytest.mark.parametrize("kind", ["keplerian", "rigid"])
+def test_distance_and_speed_bound_the_splines(kind):
+    s = inputs.make_orbit_samples(kind, T0, T0 + 1e6)
+    b = native.OrbitBounds.from_samples(s).c
+    c = oracle.Orbits.from_samples(s).coef[:9].reshape(3, 3, -1, 4)    # [spacecraft][xyz]
+    u = np.linspace(0.0, s.dt, 33)
+    x = c[..., 0:1] + u * (c[..., 1:2] + u * (c[..., 2:3] + u * c[..., 3:4]))
+    v = c[..., 1:2] + u * (2.0 * c[..., 2:3] + 3.0 * u * c[..., 3:4])
+    apart = max(np.linalg.norm(x[i] - x[(i + 1) % 3], axis=0).max() for i in range(3))
+    speed = np.linalg.norm(v, axis=1).max()
+    assert apart <= b.D_max <= 1.05 * apart
+    assert speed <= b.V_max <= 1.5 * speed
+
+
 ROUTES = [("keplerian", 1e4, 5.0, True), ("keplerian", 1e4, 10.0, True),
           ("keplerian", 1e4, 15.0, True), ("keplerian", 3e3, 2.5, True),
           ("keplerian", 3e3, 10.0, False), ("keplerian", 1e3, 5.0, False),
