@@ -37,8 +37,6 @@
 
 namespace lr {
 
-constexpr int kFirCoef = 4;                   // coefficients in time per tap
-
 // Terms of a filter row (row 2 l + i is the i-th channel that link l feeds),
 // packed: 4 bits for each link light time's multiplicity in the delay, then
 // bit 24: the term exists, bit 25: it is subtracted.  An undelayed term has
@@ -229,21 +227,23 @@ __device__ __forceinline__ void fir_shift(const OrbitView& orb, double t0, doubl
 
 // The filters of the interval as cubics in the interval's own time t in
 // [-1, 1], to the cleared W[link][k][row of the link][4] (K taps, tap k at
-// link sample o + lo + k of output o).  TRANS: for the transpose, taps in
+// link sample o + lo + k of output o).  mark: a weight that is exactly zero (a delay
+// of whole samples) leaves its tap in the stencil, though a trace only, so that a
+// NaN there still counts.  TRANS: for the transpose, taps in
 // reverse order, and the cubics moved to the link sample's time (output =
 // link sample - lo - k; inv_hw: 1 / half width in samples).
 template <int N, int GEN, bool TRANS>
 __device__ __forceinline__ void fir_build(const FirLane& f, int lo, int K, double inv_hw,
-                                          double* W, int tid) {
+                                          double* W, int tid, bool mark) {
   const int rq = tid >> 2, r = rq % 12, q = rq / 12;
   const bool direct = (f.term & 0xffffffu) == 0;
   const double sign = f.term & kFirMinusBit ? -1.0 : 1.0;
   double w[N];
   lagrange_weights<N>(f.a - f.shift, w, sign);
-  // a weight that is exactly zero (a delay of whole samples) leaves its tap in the
-  // stencil, though a trace only: a NaN there still counts
+  if (mark) {
 #pragma unroll
-  for (int m = 0; m < N; ++m) w[m] = w[m] == 0.0 ? 1e-300 : w[m];
+    for (int m = 0; m < N; ++m) w[m] = w[m] == 0.0 ? 1e-300 : w[m];
+  }
   const int kb = min(max((int)f.shift - (N / 2 - 1) - lo, 0), K - N);
   double* row = W + (r >> 1) * 8 * K + (r & 1) * 4 + (tid & 3);
   // the terms of a row are added in turn

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kBlock, 4) void tdi_fir_kernel(TdiArgs a) {
       len = fir_next(sh, p0, cnt) - p0;
       fir_shift(a.orb, t0 + (double)p0 * a.dt, a.inv_dt, sh, f, W, 48 * K, t);
     }
-    fir_build<N, GEN, false>(f, lo, K, 0.0, W, t);
+    fir_build<N, GEN, false>(f, lo, K, 0.0, W, t, bad);
     double v[2][3];
     if (!bad) {
       double S[3][2][4];
@@ -185,8 +185,8 @@ __device__ __forceinline__ void tdi_fir_adjoint_tile(const TdiAdjArgs (&a)[M],
         }
       }
     }
-    fir_build<N, GEN, true>(f, lo, K, P.inv(), W, t);
     bad = __syncthreads_or(bad);
+    fir_build<N, GEN, true>(f, lo, K, P.inv(), W, t, bad);
     const double x0 = ((double)(s0 + 2 * t - a[0].out_start) - P.c) * P.inv();
     const double x1 = ((double)(s0 + 2 * t + 1 - a[0].out_start) - P.c) * P.inv();
 #pragma unroll 1
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kBlock, 4) void fir_tables_kernel(BatchFwdArgs a) {
   const FirPiece P(q * kFirInterval, kFirInterval);
   const bool ok = fir_regular<GEN>(a.orb_t, a.t_off_t + P.c * a.dt, P.hw * a.dt, a.inv_dt, sh, f,
                                    lds_dyn, 48 * K, tid);
-  fir_build<N, GEN, false>(f, a.fir_lo, K, 0.0, lds_dyn, tid);
+  fir_build<N, GEN, false>(f, a.fir_lo, K, 0.0, lds_dyn, tid, true);
   // four taps of a link as 16 pairs, so that a lane loads them at once
   const int nq = fir_quads(K), n = 192 * nq;
   double* w = a.fir + q * n;
