@@ -139,8 +139,9 @@ def lane_ops_fwd_adjoint(grids, order, generation, share_fwd, share_adj, sky=Tru
 
 
 # ---------------------------------------------------------------------------
-# The same per (template, sample) as the kernels compute it at dt of a second
-# and more: h+ and hx as polynomials of degree d = min(N - 1, 15) per stencil
+# The same per (template, sample) as the kernels compute it where polynomials
+# and filters serve (order 7 and more at dt of a few seconds and more, smooth
+# light times): h+ and hx as polynomials of degree d = min(N - 1, 15) per stencil
 # base (mirrored pairs: (N / 2)(d + 1) + N operations per polarisation, then d
 # per position and polarisation), TDI as 12 filters of K taps with cubics in
 # time for weights (four operations per tap and filter, or four per weight,

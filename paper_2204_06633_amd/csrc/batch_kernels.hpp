@@ -130,7 +130,9 @@ __device__ __forceinline__ void fused_tdi_careful(const double* ylds, const doub
 
 // WAVE: h+ / hx synthesised from each template's parameter row (Sec. III)
 // instead of read from the caller's arrays.  A compile-time choice: with the
-// waveform code in the same kernel the array path's registers spill.
+// waveform code in the same kernel the array path's registers spill.  Two waves per
+// SIMD: LDS lets no more workgroups of the usual shapes share a CU, and the
+// projection's coefficients need the registers.
 template <int N, int GEN, int M, int BLOCK, bool WAVE>
 __global__ __launch_bounds__(BLOCK, 2)
 void fused_forward_kernel(BatchFwdArgs a) {

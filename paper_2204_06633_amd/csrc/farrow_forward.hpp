@@ -15,7 +15,7 @@
 // coefficients rule out four).  Order 25, dt = 10 s, against nine weight
 // sequences per link sample shared by two samples of a lane: 3,155,760 samples
 // 250 -> 170 us, 8640 samples 17 -> 13 us; in the fused batched forward, 32
-// templates of 1.5 million outputs, 6.40 -> 5.35 ms.
+// templates of 1.5 million outputs, 6.40 -> 5.27 ms.
 #pragma once
 
 #include "farrow.hpp"
