@@ -238,8 +238,16 @@ __device__ __forceinline__ void FarrowForward<N, BLOCK, G, PAD>::project(
   }
 }
 
+// Waves per SIMD that the projection's registers leave room for: three, or more where
+// a build asks for more (four spill the coefficients: 3,155,760 samples of order 25
+// 347 us against 252).
+#ifndef LR_PROJ_MIN_WAVES
+#define LR_PROJ_MIN_WAVES 1
+#endif
+constexpr int kProjWaves = LR_PROJ_MIN_WAVES > 3 ? LR_PROJ_MIN_WAVES : 3;
+
 template <int N>
-__global__ __launch_bounds__(kFarrowBlock, 3) void farrow_project_kernel(ProjArgs a) {
+__global__ __launch_bounds__(kFarrowBlock, kProjWaves) void farrow_project_kernel(ProjArgs a) {
   __shared__ FarrowForward<N, kFarrowBlock, 9, kFarrowSpread> sh;
   __shared__ double s_trig[2][2];
   const SkyTrig tr = load_sky(a.sky, s_trig);

@@ -30,11 +30,6 @@
 
 namespace lr {
 
-// Switch of a kernel that is no more; lr_build_config() still reports it.
-#ifndef LR_PROJ_MIN_WAVES
-#define LR_PROJ_MIN_WAVES 1
-#endif
-
 constexpr int kBlock = kTile;          // lanes per workgroup
 constexpr int kSlack = 64;             // window samples beyond the tile + taps
 constexpr int kPerLane = 2;            // forward kernels: consecutive samples per lane

@@ -336,6 +336,21 @@ def test_switch_defaults_in_the_headers():
     assert found == PRODUCT_SWITCHES
 
 
+@pytest.mark.parametrize("name", sorted(PRODUCT_SWITCHES))
+def test_every_reported_switch_is_read(name):
+    """A switch that lr_build_config() reports is used by some source beyond
+    its definition and the report itself."""
+    import re
+    csrc = os.path.join(ROOT, "paper_2204_06633_amd", "csrc")
+    uses = 0
+    for f in os.listdir(csrc):
+        if f.endswith((".hpp", ".hip", ".cpp")) and f != "build_config.hip":
+            text = re.sub(r"//[^\n]*|#ifndef LR_\w+\n#define LR_\w+ \d+", "",
+                          open(os.path.join(csrc, f)).read())
+            uses += len(re.findall(r"\b%s\b" % name, text))
+    assert uses >= 1
+
+
 def _c_functions(text):
     """(name, body) of every top-level `lr_*` function definition."""
     out = []
